@@ -4,7 +4,8 @@
 // block; the comparison of the paper's kernel benchmark, Appendix A).
 //
 // Split-KV flash decoding.  Keys are indexed in the concatenation
-// [k_cache[b][0 .. P_b-1]; k_block[b][0 .. L-1]] and cut into n_split ranges.
+// [k_cache[b][0 .. P_b-1]; k_block[b][0 .. L-1]] and cut into ranges of whole
+// 32-key tiles, as many per request as its length asks for (SpPlan).
 // One workgroup per (request b, KV head g, range s) with one wave per query
 // head of the group (GQA packing: the G heads share every K/V tile through
 // LDS).  Each 32-key tile gives Sc^T = K Q^T (keys in rows, one query per
@@ -21,6 +22,7 @@
 // it starts (a range holds at most kMaxRange keys), so the copies of a tile
 // take their page from LDS and no vector load of the page table sits among
 // the copies whose counts the ring waits on.
+#include <algorithm>
 #include <type_traits>
 
 #include "device.h"
@@ -47,7 +49,7 @@ struct SpCfg {
 };
 
 constexpr int kMaxGroup = 8;  // query heads per KV head handled by one WG
-constexpr int kMaxRange = 32768;  // keys of one split range at most
+constexpr int kMaxRange = 65536;  // keys of one split range at most
 // pages of one range at the smallest page size (32), unaligned ends included
 constexpr int kMaxRangePages = kMaxRange / 32 + 2;
 
@@ -58,13 +60,152 @@ __device__ inline int sp_page(const SoftmaxPrefixArgs& a, const int32_t* ptab, i
   return min(max(pg, 0), a.n_pages - 1);
 }
 
+// Keys of request b: its cached prefix (clamped) and the block.
+__device__ inline int sp_keys(const SoftmaxPrefixArgs& a, int b) {
+  return min(max(a.prefix_len[b], 0), a.max_prefix) + a.s.L;
+}
+
+__device__ inline int sp_tiles(const SoftmaxPrefixArgs& a, int b) {
+  return (sp_keys(a, b) + kTile - 1) / kTile;
+}
+
+// How the requests' keys are cut.  The lengths are known on the device only,
+// so every workgroup works the cut out for itself, from prefix_len alone and
+// with the same result: request b gets ceil(tiles_b / c) ranges, numbered
+// through over the requests (its first is number base_b), and range s of
+// request b takes an even share of its tiles.  The tiles per range c is the
+// candidate with the least estimated time, rounds * (c + the cost of a
+// range): rounds of `fill` ranges (the workgroups the chip holds at once, per
+// KV head), and a range costs its start, its partial result and that result's
+// merge, about kRangeCost tiles.  Candidates lie around the even share of the
+// chip; the last one cuts the longest request into limit / B ranges, so that
+// all ranges fit the grid and the workspace.
+// Equal cuts of max_prefix into n_split ranges, as it was, make 2048
+// workgroups whatever the lengths: four rounds and a merge where one round of
+// whole requests fills the chip (128 requests of 32768 keys: 1.70 against
+// 1.54 ms, the loop below included), and ranges past a short request's end
+// that still write, and have merged, an empty result (24 requests of 1 to
+// 8192 keys: 104 against 76 us; 8 of 32768: 232 against 137 us).  A round and
+// a half (fill for three or four workgroups per CU) is slower: 1.63 ms,
+// 114 us, 220 us.
+struct SpPlan {
+  int c;      // tiles per range, before the even share
+  bool whole; // every request is one range
+};
+constexpr int kRangeCost = 10;
+constexpr int kCand = 16;        // candidates; kWave / kCand lanes share one
+constexpr int kPlanTiles = 256;  // requests staged in LDS at most
+
+// tiles: LDS scratch of kPlanTiles + 2 ints.  All threads of the workgroup;
+// the first wave plans.
+__device__ inline SpPlan sp_plan(const SoftmaxPrefixArgs& a, int fill, int limit, int* tiles) {
+  const int B = a.s.B, tid = threadIdx.x;
+  if (a.n_split == 1) return SpPlan{1 << 24, true};
+  if (tid < kWave) {
+    int total = 0, most = 0;
+    for (int b0 = tid; b0 < B; b0 += kWave) {
+      const int nt = sp_tiles(a, b0);
+      if (B <= kPlanTiles) tiles[b0] = nt;
+      total += nt;
+      most = max(most, nt);
+    }
+    for (int x = 1; x < kWave; x <<= 1) {
+      total += __shfl_xor(total, x);
+      most = max(most, __shfl_xor(most, x));
+    }
+    __builtin_amdgcn_wave_barrier();  // (tiles: written and read by this wave)
+    const int share = max(1, (total + fill - 1) / fill);
+    const int cand = tid % kCand, sub = tid / kCand;
+    // 1/4, 1/3, 1/2, 3/4, then from 1 on in steps of 1/16 to 1 1/2, 2, 4
+    const int num = cand < 4 ? (cand == 0 ? 12 : cand == 1 ? 16 : cand == 2 ? 24 : 36)
+                    : cand < 13 ? 48 + 3 * (cand - 4) : cand == 13 ? 96 : 192;
+    int c = (int)(((long)share * num + 47) / 48);
+    c = min(max(c, 4), kMaxRange / kTile);
+    const int least = max(1, limit / B);
+    if (cand == kCand - 1) c = (most + least - 1) / least;
+    const float rc = 1.0f / (float)c;
+    int sum = 0;
+    for (int b0 = sub; b0 < B; b0 += kWave / kCand) {
+      const int x = B <= kPlanTiles ? tiles[b0] : sp_tiles(a, b0);
+      const int n = (int)((float)x * rc);  // x / c, within one
+      sum += n + (n * c < x ? 1 : 0);      // one too many at worst, never too few
+    }
+    for (int x = kCand; x < kWave; x <<= 1) sum += __shfl_xor(sum, x);
+    const int rounds = (sum + fill - 1) / fill;
+    const float cost = sum <= limit || cand == kCand - 1
+                           ? (float)rounds * (float)(min(c, most) + (sum > B ? kRangeCost : 0))
+                           : INFINITY;
+    float best = cost;
+    for (int x = 1; x < kWave; x <<= 1) best = fminf(best, __shfl_xor(best, x));
+    const int at = __builtin_ctzll(__ballot(cost == best));
+    const int pick = __builtin_amdgcn_readlane(c, at);
+    if (tid == 0) {
+      tiles[kPlanTiles] = pick;
+      tiles[kPlanTiles + 1] = most <= pick;
+    }
+  }
+  __syncthreads();
+  return SpPlan{__builtin_amdgcn_readfirstlane(tiles[kPlanTiles]),
+                __builtin_amdgcn_readfirstlane(tiles[kPlanTiles + 1]) != 0};
+}
+
+// Ranges of a request of nt tiles.
+__device__ inline int sp_ranges(const SpPlan& p, int nt) { return (nt + p.c - 1) / p.c; }
+
+// Range number r of the plan: its request, its place there, how many ranges
+// that request has and its keys lo .. hi-1.  b = -1: no such range.
+struct SpRange {
+  int b, s, n, lo, hi;
+};
+__device__ inline SpRange sp_range(const SoftmaxPrefixArgs& a, const SpPlan& p, int r, int lane) {
+  const int B = a.s.B;
+  int base = 0;
+  for (int b0 = 0; b0 < B; b0 += kWave) {
+    const int nt = b0 + lane < B ? sp_tiles(a, b0 + lane) : 0;
+    const int n = b0 + lane < B ? sp_ranges(p, nt) : 0;
+    int end = n;  // inclusive sum over the lanes
+    for (int x = 1; x < kWave; x <<= 1) {
+      const int y = __shfl_up(end, x);
+      if (lane >= x) end += y;
+    }
+    const int all = __builtin_amdgcn_readlane(end, kWave - 1);
+    if (r < base + all) {
+      const int at = __builtin_ctzll(__ballot(r < base + end));
+      SpRange q;
+      q.b = b0 + at;
+      q.n = __builtin_amdgcn_readlane(n, at);
+      q.s = r - base - (__builtin_amdgcn_readlane(end, at) - q.n);
+      const int tiles = __builtin_amdgcn_readlane(nt, at);
+      // an even share of the tiles: the first tiles % n ranges take one more
+      const int each = tiles / q.n, more = tiles % q.n;
+      const int t0 = q.s * each + min(q.s, more);
+      q.lo = t0 * kTile;
+      q.hi = min((t0 + each + (q.s < more ? 1 : 0)) * kTile, sp_keys(a, q.b));
+      return q;
+    }
+    base += all;
+  }
+  return SpRange{-1, 0, 0, 0, 0};
+}
+
+// Partial results in the workspace, by range number r: rows of D floats
+// [r][head][query], then (max, sum) pairs in the same order; at most n_split
+// ranges per request on average.
+__device__ inline size_t sp_row(const SoftmaxPrefixArgs& a, int r, int h, int i) {
+  return ((size_t)r * a.s.Hq + h) * a.s.L + i;
+}
+template <int D>
+__device__ inline float* sp_ml(const SoftmaxPrefixArgs& a) {
+  return (float*)a.ws + (size_t)a.s.B * a.n_split * a.s.Hq * a.s.L * D;
+}
+
 // One wave per query head of the KV group; 32-key tiles double-buffered in
 // LDS: the tile after next is loaded into registers while the current one is
 // computed, and the next one is moved from registers into the free buffer at
 // the end of the step, so one barrier per tile orders everything.
 template <typename T, int D, int NG, bool PAGED>
 __global__ __launch_bounds__(kWave* NG) void hyb_sp_partial_kernel(
-    SoftmaxPrefixArgs a, int chunk) {
+    SoftmaxPrefixArgs a, int fill, int limit) {
   typedef SpCfg<T, D, NG> C;
   typedef typename C::M M;
   typedef typename C::op_t op_t;
@@ -75,15 +216,13 @@ __global__ __launch_bounds__(kWave* NG) void hyb_sp_partial_kernel(
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int li = lane & 31, hh = lane >> 5;
   const int Hq = a.s.Hq, Hkv = a.s.Hkv, L = a.s.L, G = Hq / Hkv;
-  const int ns = a.n_split, Pmax = a.max_prefix;
-  const int s = blockIdx.x % ns;
-  const int bg = blockIdx.x / ns;
-  const int b = bg / Hkv, g = bg % Hkv, h = g * G + w;
-  int P = a.prefix_len[b];
-  P = P < 0 ? 0 : (P > Pmax ? Pmax : P);
-  const int N = P + L;
-  const int lo = s * chunk;
-  const int hi = min(lo + chunk, N);
+  const int Pmax = a.max_prefix;
+  const int g = blockIdx.x % Hkv, r = blockIdx.x / Hkv, h = g * G + w;
+  __shared__ int plan[kPlanTiles + 2];
+  const SpRange rg = sp_range(a, sp_plan(a, fill, limit, plan), r, lane);
+  if (rg.b < 0) return;  // uniform: past the plan's last range
+  const int b = rg.b, lo = rg.lo, hi = rg.hi;
+  const int P = sp_keys(a, b) - L;
   const size_t qstride = (size_t)Hq * D, kstride = (size_t)Hkv * D;
 
   op_t qop[C::KD];
@@ -231,8 +370,8 @@ __global__ __launch_bounds__(kWave* NG) void hyb_sp_partial_kernel(
 
   // Partial result of this range: unnormalised O, running max and sum.
   if (li >= L) return;
-  if (ns == 1) {
-    // one range: the result is final, normalised here (no combine launch)
+  if (rg.n == 1) {
+    // one range: the result is final, normalised here
     const float inv = 1.0f / l;
     const size_t ob = (((size_t)b * L + li) * Hq + h) * D;
 #pragma unroll
@@ -245,9 +384,9 @@ __global__ __launch_bounds__(kWave* NG) void hyb_sp_partial_kernel(
       }
     return;
   }
-  const size_t row = (((size_t)b * Hq + h) * ns + s) * L + li;
+  const size_t row = sp_row(a, r, h, li);
   float* wacc = (float*)a.ws + row * D;
-  float* wml = (float*)a.ws + (size_t)a.s.B * Hq * ns * L * D + row * 2;
+  float* wml = sp_ml<D>(a) + row * 2;
 #pragma unroll
   for (int ct = 0; ct < C::NCT; ++ct)
 #pragma unroll
@@ -261,17 +400,26 @@ __global__ __launch_bounds__(kWave* NG) void hyb_sp_partial_kernel(
 }
 
 
-// bf16 with 1, 2, 4 or 8 query heads per KV head: the K/V tiles reach LDS by
-// direct global->LDS copies into a ring of R = 4 tile slots, three tiles in
-// flight while one is computed, with no registers held for them.  Each copy
-// instruction reads whole rows, 16 bytes per lane; chunk c of a staged row t
-// sits at position c ^ swz(t), so the rows one operand read touches fall in
-// distinct LDS banks.  The slots are distinct arrays and the tile loop is
-// unrolled over them, so every copy and every read names its slot at
-// compile time.  A wave waits only for its own copies of the tile it is
-// about to read (vmcnt counts the later tiles' copies still in flight), then
-// one barrier per tile makes all of them visible and frees the slot the
-// next copy reuses.
+// bf16 with 1, 2, 4 or 8 query heads per KV head: the K and V tiles reach
+// LDS by direct global->LDS copies into two rings of R = 4 tile slots, three
+// tiles in flight while one is computed, with no registers held for them.
+// Each copy instruction reads whole rows, 16 bytes per lane; chunk c of a
+// staged K row t sits at position c ^ swz(t), of a V row at c ^ vswz(t), so
+// the rows one operand read touches fall in distinct LDS banks (a K operand
+// reads one chunk of 32 rows, a transposing V read four chunks of 4 rows per
+// half wave).  The slots are distinct arrays and the
+// tile loop is unrolled over them, so every copy and every read names its
+// slot at compile time.  A wave waits only for its own copies of the tiles it
+// is about to read (vmcnt counts the later tiles' copies still in flight),
+// then one barrier per tile makes all of them visible and frees the slots the
+// next copies reuse.
+//
+// What bounds the loop is each wave's chain, not the copies: scores (8
+// dependent MFMAs), maximum, exponentials, P V (8 MFMAs).  So step n forms
+// the scores of tile n + 1 while it takes the softmax of tile n: two
+// independent chains whose MFMAs and VALU instructions interleave.  That is
+// why K runs one tile ahead of V in its ring.  At 128 requests of 32768 keys:
+// 1.72 ms (5.0 TB/s) as one chain, 1.51 ms (5.7 TB/s) so.
 template <int D>
 struct SpRing {
   static constexpr int EPC = 8;                      // bf16 per 16 bytes
@@ -281,6 +429,7 @@ struct SpRing {
   static constexpr int IK = kTile / RPI;             // copies per 32-row tile
   static constexpr int R = 4;                        // ring slots
   __device__ static constexpr int swz(int t) { return (t / RP256) % CPR; }
+  __device__ static constexpr int vswz(int t) { return 4 * ((t / RP256) % (CPR / 4)); }
 };
 
 template <int D>
@@ -290,40 +439,41 @@ struct alignas(16) SpSlot {
 };
 
 template <int D, int NG, bool PAGED>
-__global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefixArgs a, int chunk) {
+__global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefixArgs a, int fill,
+                                                                    int limit) {
   typedef Mma<bf16> M;
   typedef typename M::op_t op_t;
   typedef SpRing<D> RG;
   constexpr int E = M::E, KW = M::KW, KD = D / KW, KL = kTile / KW, NCT = D / kTile;
   constexpr int EPC = RG::EPC, CPR = RG::CPR, RPI = RG::RPI, IK = RG::IK, R = RG::R;
-  constexpr int IPW = 2 * IK / NG;  // copies per wave per tile
+  constexpr int IPW = 2 * IK / NG;  // copies per wave and step
   static_assert(IPW * NG == 2 * IK, "copies split evenly over the waves");
+  static_assert(3 * IPW <= 63, "a wave's copies in flight fit vmcnt");
   __shared__ SpSlot<D> s0, s1, s2, s3;
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int li = lane & 31, hh = lane >> 5;
   const int Hq = a.s.Hq, Hkv = a.s.Hkv, L = a.s.L, G = Hq / Hkv;
-  const int ns = a.n_split, Pmax = a.max_prefix;
+  const int Pmax = a.max_prefix;
   // The KV head varies fastest: the Hkv workgroups that read the same
   // token rows of the cache (each its 1/Hkv share of every row) start
   // together.
-  const int g = blockIdx.x % Hkv;
-  const int s = (blockIdx.x / Hkv) % ns;
-  const int b = blockIdx.x / (Hkv * ns), h = g * G + w;
-  int P = a.prefix_len[b];
-  P = P < 0 ? 0 : (P > Pmax ? Pmax : P);
-  const int N = P + L;
-  const int lo = s * chunk;
-  const int hi = min(lo + chunk, N);
-  const int ntiles = hi > lo ? (hi - lo + kTile - 1) / kTile : 0;
+  const int g = blockIdx.x % Hkv, r = blockIdx.x / Hkv, h = g * G + w;
+  __shared__ int plan[kPlanTiles + 2];
+  const SpRange rg = sp_range(a, sp_plan(a, fill, limit, plan), r, lane);
+  if (rg.b < 0) return;  // uniform: past the plan's last range
+  const int b = rg.b, lo = rg.lo, hi = rg.hi;
+  const int P = sp_keys(a, b) - L;
+  const int ntiles = (hi - lo + kTile - 1) / kTile;
   const size_t qstride = (size_t)Hq * D, kstride = (size_t)Hkv * D;
 
   op_t qop[KD];
   {
-    const bf16* qrow = (const bf16*)a.q + ((size_t)b * L * Hq + h) * D + (size_t)li * qstride + hh * E;
+    const bf16* qrow =
+        (const bf16*)a.q + ((size_t)b * L * Hq + h) * D + (size_t)min(li, L - 1) * qstride + hh * E;
 #pragma unroll
-    for (int ks = 0; ks < KD; ++ks) qop[ks] = li < L ? load_op<bf16>(qrow + ks * KW) : M::zero();
+    for (int ks = 0; ks < KD; ++ks) qop[ks] = keep_if<bf16>(li < L, load_op<bf16>(qrow + ks * KW));
   }
   // contiguous: this request's rows; paged: the pool, at KV head g
   const bf16* kc = (const bf16*)a.k_cache + ((PAGED ? 0 : (size_t)b * Pmax * Hkv) + g) * D;
@@ -346,113 +496,116 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
   // descriptor whose base is the tile's first row (a scalar) and, per lane
   // and copy, the 32-bit offset of its 16-byte piece, which is the same for
   // every tile.  Tiles that reach past the cache or the range take the
-  // general path below.
+  // general path below.  Copy ins of a step is K's (kv = 0) or V's (kv = 1);
+  // a wave's copies are all of one kind, except with one wave (NG = 1).
   int voff[IPW];
 #pragma unroll
   for (int u = 0; u < IPW; ++u) {
     const int ins = w * IPW + u, i = ins % IK;
     const int t = i * RPI + lane / CPR, pos = lane % CPR;
-    voff[u] = (int)(((size_t)t * kstride + (size_t)((pos ^ RG::swz(t)) * EPC)) * sizeof(bf16));
+    const int sw = ins < IK ? RG::swz(t) : RG::vswz(t);
+    voff[u] = (int)(((size_t)t * kstride + (size_t)((pos ^ sw) * EPC)) * sizeof(bf16));
   }
   const int cend = min(hi, P);  // keys below this come from the cache
-  auto issue_fast = [&](int n, SpSlot<D>& sl) __attribute__((always_inline)) {
+  constexpr int NKV = NG == 1 ? 2 : 1;      // kinds of copies per wave
+  constexpr int IPK = IPW / NKV;            // copies per kind
+  // This wave's copies u0 .. u0 + IPK - 1, of kind kv, of tile n into dst
+  // (keys past the range read the range's last key, in bounds, and are
+  // masked below).
+  auto issue_kind = [&](int kv, int u0, int n, bf16* dst) __attribute__((always_inline)) {
     const int j0 = lo + n * kTile;
-    const bf16* kt = kc;
-    const bf16* vt = vc;
-    if constexpr (PAGED) {
-      const int pi = j0 >> a.page_shift;
-      const ptrdiff_t sh =
-          ((ptrdiff_t)__builtin_amdgcn_readfirstlane(pages[pi - p0]) - pi) * ((ptrdiff_t)kstride << a.page_shift);
-      kt += sh;
-      vt += sh;
-    }
-    kt += (size_t)j0 * kstride;
-    vt += (size_t)j0 * kstride;
-    const int span = (int)((size_t)kTile * kstride * sizeof(bf16));
-    const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(kt), 0, span, kBufferWord3);
-    const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(vt), 0, span, kBufferWord3);
-#pragma unroll
-    for (int u = 0; u < IPW; ++u) {
-      const int ins = w * IPW + u, kv = ins / IK, i = ins % IK;
-      bf16* dst = (kv == 0 ? sl.k : sl.v) + i * RPI * D;
-      buf_to_lds16(kv == 0 ? rk : rv, dst, voff[u], 0);
-    }
-  };
-
-  // This wave's copies of tile n (keys past the range read the range's last
-  // key, in bounds, and are masked below).
-  auto issue = [&](int n, SpSlot<D>& sl) __attribute__((always_inline)) {
-    const int j0 = lo + n * kTile;
+    const bf16* cb = kv == 0 ? kc : vc;
     if (j0 + kTile <= cend) {
-      issue_fast(n, sl);
+      if constexpr (PAGED) {
+        const int pi = j0 >> a.page_shift;
+        cb += ((ptrdiff_t)__builtin_amdgcn_readfirstlane(pages[pi - p0]) - pi) *
+              ((ptrdiff_t)kstride << a.page_shift);
+      }
+      cb += (size_t)j0 * kstride;
+      const int span = (int)((size_t)kTile * kstride * sizeof(bf16));
+      const __amdgpu_buffer_rsrc_t rs =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(cb), 0, span, kBufferWord3);
+#pragma unroll
+      for (int u = u0; u < u0 + IPK; ++u) buf_to_lds16(rs, dst + (w * IPW + u) % IK * RPI * D, voff[u], 0);
       return;
     }
-    const bf16* kcb = kc;
-    const bf16* vcb = vc;
     if constexpr (PAGED) {
       // the tile's rows (clamped to the range, all >= j0) lie in the page of
       // row j0: that page's base, shifted so that base + j * kstride is row j
       if (j0 < P) {
         const int pi = j0 >> a.page_shift;
-        const ptrdiff_t sh = ((ptrdiff_t)pages[pi - p0] - pi) * ((ptrdiff_t)kstride << a.page_shift);
-        kcb += sh;
-        vcb += sh;
+        cb += ((ptrdiff_t)pages[pi - p0] - pi) * ((ptrdiff_t)kstride << a.page_shift);
       }
     }
+    const bf16* blk = kv == 0 ? kbk : vbk;
 #pragma unroll
-    for (int u = 0; u < IPW; ++u) {
-      const int ins = w * IPW + u, kv = ins / IK, i = ins % IK;
+    for (int u = u0; u < u0 + IPK; ++u) {
+      const int i = (w * IPW + u) % IK;
       const int t = i * RPI + lane / CPR, pos = lane % CPR;
       const int j = min(j0 + t, hi - 1);
-      const bf16* cb = kv == 0 ? kcb : vcb;
-      const bf16* row = kv == 0 ? (j < P ? cb + (size_t)j * kstride : kbk + (size_t)(j - P) * kstride)
-                                : (j < P ? cb + (size_t)j * kstride : vbk + (size_t)(j - P) * kstride);
-      bf16* dst = (kv == 0 ? sl.k : sl.v) + i * RPI * D;
+      const bf16* row = j < P ? cb + (size_t)j * kstride : blk + (size_t)(j - P) * kstride;
       __builtin_amdgcn_global_load_lds(
-          (const __attribute__((address_space(1))) void*)(row + (pos ^ RG::swz(t)) * EPC),
-          (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+          (const __attribute__((address_space(1))) void*)(row + (pos ^ (kv == 0 ? RG::swz(t) : RG::vswz(t))) * EPC),
+          (__attribute__((address_space(3))) void*)(dst + i * RPI * D), 16, 0, 0);
+    }
+  };
+  // The copies of step n: K of tile nk and V of tile nv, where they exist.
+  auto issue = [&](int nk, SpSlot<D>& sk, int nv, SpSlot<D>& sv) __attribute__((always_inline)) {
+    if constexpr (NG == 1) {
+      if (nk < ntiles) issue_kind(0, 0, nk, sk.k);
+      if (nv >= 0 && nv < ntiles) issue_kind(1, IPK, nv, sv.v);
+    } else {
+      const int kv = w * IPW / IK, n = kv == 0 ? nk : nv;
+      if (n >= 0 && n < ntiles) issue_kind(kv, 0, n, kv == 0 ? sk.k : sv.v);
     }
   };
 
   // Scores and the running maximum m are kept in the log2 domain (scaled by
-  // log2 e with 1/sqrt(d)), so each weight is one subtraction and one exp2;
+  // log2 e with 1/sqrt(d)), so each weight is one fma and one exp2;
   // m is converted back where it is written out for the combine.
   const float scale = 1.4426950408889634f / sqrtf((float)D);
-  // The running sum of the weights comes from the MFMAs, as the product of
-  // P^T with a tile of ones (every row of lsum holds it; only row 0 is kept
-  // rescaled, the one that is read), so it is the sum of the same rounded
-  // weights that enter P V.
+  // The running sum of the weights comes from the MFMAs, so it is the sum of
+  // the same rounded weights that enter P V: a 16x16 product whose column
+  // li % 16 holds, as its contraction quarters, the keys of queries li % 16
+  // (even quarters) and li % 16 + 16 (odd ones).  Row x of the left operand
+  // is one on the quarters of the parity of x / 4, which is that of the lane
+  // that receives the row, so register 0 is the sum of the lane's own query
+  // (only that register is kept rescaled).
   float m = -INFINITY;
-  f32x16 acc[NCT], lsum = {};
+  f32x16 acc[NCT];
+  f32x4 lsum = {};
 #pragma unroll
   for (int ct = 0; ct < NCT; ++ct) acc[ct] = f32x16{};
   op_t ones;
 #pragma unroll
-  for (int e = 0; e < E; ++e) ones[e] = (bf16)1.0f;
+  for (int e = 0; e < E; ++e) ones[e] = (bf16)(((lane >> 4) ^ (lane >> 2)) & 1 ? 0.0f : 1.0f);
 
-  auto compute = [&](int n, const SpSlot<D>& sl) __attribute__((always_inline)) {
-    const int j0 = lo + n * kTile;
-    f32x16 sc = {};
+  // Raw scores of a tile: keys in rows, queries in columns.
+  auto k_op = [&](const bf16* kt, int ks) __attribute__((always_inline)) -> op_t {
+    const int c = 2 * ks + hh;  // 16-byte chunk of elements ks*KW + hh*E
+    return load_op<bf16>(&kt[li * D + (c ^ RG::swz(li)) * EPC]);
+  };
+  // Scores of the tile of the current step, already in the running maximum
+  // (and the accumulators rescaled to it).
+  f32x16 sc;
+  // Takes the scores of tile n into sc and the running maximum.  The
+  // accumulators are rescaled only when some query's maximum rose: once the
+  // maximum settles most tiles skip the 64 multiplies.  Keys past the range,
+  // in the range's last tile only, are masked.
+  auto take_scores = [&](auto check, int n, const f32x16& s) __attribute__((always_inline)) {
+    sc = s;
+    if constexpr (decltype(check)::value) {
+      const int j0 = lo + n * kTile;
+      if (j0 + kTile > hi) {  // uniform
 #pragma unroll
-    for (int ks = 0; ks < KD; ++ks) {
-      const int c = 2 * ks + hh;  // 16-byte chunk of elements ks*KW + hh*E
-      sc = M::mma(load_op<bf16>(&sl.k[li * D + (c ^ RG::swz(li)) * EPC]), qop[ks], sc);
+        for (int i = 0; i < 16; ++i) sc[i] = j0 + row_of(i, hh) < hi ? sc[i] : -INFINITY;
+      }
     }
-    float p[16];
-    if (j0 + kTile <= hi) {  // (uniform) a full tile needs no range masks
+    float mt = sc[0];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) p[i] = sc[i] * scale;
-    } else {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) p[i] = j0 + row_of(i, hh) < hi ? sc[i] * scale : -INFINITY;
-    }
-    float mt = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) mt = fmaxf(mt, p[i]);
+    for (int i = 1; i < 16; ++i) mt = fmaxf(mt, sc[i]);
     mt = fmaxf(mt, xor32(mt));
-    const float mn = fmaxf(m, mt);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(p[i] - mn);
+    const float mn = fmaxf(m, mt * scale);
     if (__any(mn > m)) {
       const float corr = __builtin_amdgcn_exp2f(m - mn);
       lsum[0] *= corr;
@@ -462,34 +615,80 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
         for (int i = 0; i < 16; ++i) acc[ct][i] *= corr;
     }
     m = mn;
+  };
+
+  // Weights and P V of tile n (its scores in sc, its V in vt) and the scores
+  // of tile n + 1 (its K in kt; not with LAST), then that tile's maximum.
+  auto compute = [&](auto last, auto check, int n, const bf16* kt, const bf16* vt) __attribute__((always_inline)) {
+    constexpr bool LAST = decltype(last)::value;
+    op_t kop[KD];
+    if constexpr (!LAST) {
+#pragma unroll
+      for (int ks = 0; ks < KD; ++ks) kop[ks] = k_op(kt, ks);
+    }
+    f32x16 sn = {};
+    if constexpr (!LAST) {
+#pragma unroll
+      for (int ks = 0; ks < KD; ++ks) sn = M::mma(kop[ks], qop[ks], sn);
+    }
+    float p[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[i], scale, -m));
+    op_t pop[KL];
+#pragma unroll
+    for (int ks = 0; ks < KL; ++ks) pop[ks] = cvt_op<bf16>(&p[ks * E]);
     // V^T operands by transposing reads: in each 16-lane quarter lane i
     // addresses key kb + i/4 at columns cb + 4*(i%4) .. +3 and receives
     // keys kb .. kb+3 of column cb + i.
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     const int qi = lane & 15;
+    op_t vop[NCT][KL];
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) {
       const int col = ct * kTile + 16 * ((lane >> 4) & 1) + 4 * (qi & 3);
 #pragma unroll
       for (int ks = 0; ks < KL; ++ks) {
         auto piece = [&](int t) {
-          const bf16* src = &sl.v[t * D + ((col / EPC) ^ RG::swz(t)) * EPC + col % EPC];
+          // (t = kb + 8n: vswz(t) is that of the lane's qi / 4)
+          const bf16* src = &vt[t * D + ((col / EPC) ^ RG::vswz(qi / 4)) * EPC + col % EPC];
           return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)src);
         };
         const int kb = 16 * ks + 4 * hh + qi / 4;
         const s16x4 x0 = piece(kb), x1 = piece(kb + 8);
-        const op_t va = __builtin_bit_cast(op_t, __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7));
-        acc[ct] = M::mma(va, cvt_op<bf16>(&p[ks * E]), acc[ct]);
+        vop[ct][ks] = __builtin_bit_cast(op_t, __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7));
       }
     }
 #pragma unroll
-    for (int ks = 0; ks < KL; ++ks) lsum = M::mma(ones, cvt_op<bf16>(&p[ks * E]), lsum);
+    for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+      for (int ks = 0; ks < KL; ++ks) acc[ct] = M::mma(vop[ct][ks], pop[ks], acc[ct]);
+#pragma unroll
+    for (int ks = 0; ks < KL; ++ks) lsum = Mma16<bf16>::mma(ones, pop[ks], lsum);
+    if constexpr (!LAST) {
+      // The order of issue: K's operands; the score MFMAs with the weights
+      // between them, V's operands requested behind the first half of them;
+      // then P V with the next tile's maximum.
+      __builtin_amdgcn_sched_group_barrier(0x100, KD, 0);  // LDS reads
+#pragma unroll
+      for (int ks = 0; ks < KD / 2; ++ks) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // an MFMA
+        __builtin_amdgcn_sched_group_barrier(0x402, 6, 0);  // VALU, exp
+      }
+#pragma unroll
+      for (int ks = KD / 2; ks < KD; ++ks) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 4 * NCT * KL / KD, 0);
+        __builtin_amdgcn_sched_group_barrier(0x402, 6, 0);
+      }
+      take_scores(check, n + 1, sn);
+    }
   };
 
-  // Wait for this wave's copies of tile n, with `later` tiles issued after
-  // it still in flight.
-  auto wait_tile = [&](int later) __attribute__((always_inline)) {
-    if (later >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * IPW) : "memory");
+  // Wait for this wave's copies of the tiles of a step, with at most `later`
+  // steps' copies issued after them still in flight.
+  auto wait_step = [&](int later) __attribute__((always_inline)) {
+    if (later >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * IPW) : "memory");
+    else if (later == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * IPW) : "memory");
     else if (later == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(IPW) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   };
@@ -499,28 +698,57 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
     else if constexpr (decltype(S)::value == 2) return s2;
     else return s3;
   };
-  auto step = [&](int n, auto S) __attribute__((always_inline)) {
+  // A wave's last tile whose copies it must see: V's wave n, K's wave n + 1.
+  // With one wave, a step's copies are K n + 1 and V n; whole steps are
+  // counted while both kinds are still issued.
+  const int ahead = NG == 1 || w * IPW / IK == 0 ? 1 : 0;
+  auto step = [&](int n, auto S, auto check) __attribute__((always_inline)) {
     constexpr int SV = decltype(S)::value;
-    wait_tile(min(R - 2, ntiles - 1 - n));
-    lds_barrier_nodrain();  // tile n visible everywhere; slot of tile n-1 free
-    if (n + R - 1 < ntiles) issue(n + R - 1, slot(std::integral_constant<int, (SV + R - 1) % R>{}));
-    compute(n, slot(S));
+    const int later = ntiles - 1 - n - ahead;
+    if constexpr (NG == 1) wait_step(later >= 2 ? 2 : 0);
+    else wait_step(min(2, later));
+    lds_barrier_nodrain();  // K n+1 and V n visible everywhere; K n's and V n-1's slots free
+    issue(n + R, slot(S), n + R - 1, slot(std::integral_constant<int, (SV + R - 1) % R>{}));
+    compute(std::false_type{}, check, n, slot(std::integral_constant<int, (SV + 1) % R>{}).k, slot(S).v);
   };
 
-  if (0 < ntiles) issue(0, s0);
-  if (1 < ntiles) issue(1, s1);
-  if (2 < ntiles) issue(2, s2);
-  for (int n = 0; n < ntiles; n += R) {
-    step(n, std::integral_constant<int, 0>{});
-    if (n + 1 < ntiles) step(n + 1, std::integral_constant<int, 1>{});
-    if (n + 2 < ntiles) step(n + 2, std::integral_constant<int, 2>{});
-    if (n + 3 < ntiles) step(n + 3, std::integral_constant<int, 3>{});
+  // Copies of K 0 .. R-1 and V 0 .. R-2, in the order of the steps' copies.
+  issue(0, s0, -1, s0);
+  issue(1, s1, 0, s0);
+  issue(2, s2, 1, s1);
+  issue(3, s3, 2, s2);
+  if constexpr (NG == 1) wait_step(ntiles >= R ? 3 : 0);
+  else wait_step(ahead ? min(3, ntiles - 1) : 3);  // (V's waves need nothing yet)
+  lds_barrier_nodrain();
+  const std::false_type no{};
+  const std::true_type yes{};
+  {
+    f32x16 s = {};
+#pragma unroll
+    for (int ks = 0; ks < KD; ++ks) s = M::mma(k_op(s0.k, ks), qop[ks], s);
+    take_scores(yes, 0, s);
   }
+  int n = 0;
+  for (; n + R + 1 < ntiles; n += R) {
+    step(n, std::integral_constant<int, 0>{}, no);
+    step(n + 1, std::integral_constant<int, 1>{}, no);
+    step(n + 2, std::integral_constant<int, 2>{}, no);
+    step(n + 3, std::integral_constant<int, 3>{}, no);
+  }
+  const int rest = ntiles - n;  // 1 .. R + 1
+  if (rest > 1) step(n, std::integral_constant<int, 0>{}, yes);
+  if (rest > 2) step(n + 1, std::integral_constant<int, 1>{}, yes);
+  if (rest > 3) step(n + 2, std::integral_constant<int, 2>{}, yes);
+  if (rest > 4) step(n + 3, std::integral_constant<int, 3>{}, yes);
+  // the last tile: every copy has landed
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  lds_barrier_nodrain();
+  compute(yes, yes, ntiles - 1, nullptr, rest == 2 ? s1.v : rest == 3 ? s2.v : rest == 4 ? s3.v : s0.v);
 
   if (li >= L) return;
   const float l = lsum[0];
-  if (ns == 1) {
-    // one range: the result is final, normalised here (no combine launch)
+  if (rg.n == 1) {
+    // one range: the result is final, normalised here
     const float inv = 1.0f / l;
     const size_t ob = (((size_t)b * L + li) * Hq + h) * D;
 #pragma unroll
@@ -533,9 +761,9 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
       }
     return;
   }
-  const size_t row = (((size_t)b * Hq + h) * ns + s) * L + li;
+  const size_t row = sp_row(a, r, h, li);
   float* wacc = (float*)a.ws + row * D;
-  float* wml = (float*)a.ws + (size_t)a.s.B * Hq * ns * L * D + row * 2;
+  float* wml = sp_ml<D>(a) + row * 2;
 #pragma unroll
   for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
@@ -548,42 +776,55 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
   }
 }
 
-// Merge of the n_split partial results.  A thread handles 4 columns of one
-// (request, head, query) row (16-byte loads); a workgroup of 256 threads
-// covers 256 / (D/4) rows.
+// Merge of the partial results of the requests that have several ranges.  A
+// workgroup's unit of work is RPB rows of a (request, head), a thread 4
+// columns of a row (16-byte loads); loads of several ranges are in flight at
+// once.
 template <typename T, int D>
-__global__ __launch_bounds__(256) void hyb_sp_combine_kernel(SoftmaxPrefixArgs a) {
+__global__ __launch_bounds__(256) void hyb_sp_combine_kernel(SoftmaxPrefixArgs a, int fill, int limit) {
   constexpr int TPR = D / 4;              // threads per row
-  constexpr int RPB = 256 / TPR;          // rows per workgroup
-  const int Hq = a.s.Hq, L = a.s.L, ns = a.n_split;
-  const size_t nrows = (size_t)a.s.B * Hq * L;
-  const size_t r = (size_t)blockIdx.x * RPB + threadIdx.x / TPR;
-  if (r >= nrows) return;
-  const int c = (threadIdx.x % TPR) * 4;
-  const int i = (int)(r % L);
-  const size_t bh = r / L;
-  const int b = (int)(bh / Hq), h = (int)(bh % Hq);
-  const size_t row0 = (bh * ns) * L + i;
+  constexpr int RPB = 256 / TPR;          // rows per unit
+  __shared__ int plan[kPlanTiles + 2];
+  const SpPlan p = sp_plan(a, fill, limit, plan);
+  if (p.whole) return;  // every row is already written out
+  const int Hq = a.s.Hq, L = a.s.L, lane = threadIdx.x & (kWave - 1);
+  const int upb = (L + RPB - 1) / RPB;    // units of a (request, head)
   const float* wacc = (const float*)a.ws;
-  const float* wml = wacc + (size_t)a.s.B * Hq * ns * L * D;
-  float M = -INFINITY;
-  for (int s = 0; s < ns; ++s) M = fmaxf(M, wml[(row0 + (size_t)s * L) * 2]);
-  f32x4 num = {0.0f, 0.0f, 0.0f, 0.0f};
-  float den = 0.0f;
-  for (int s = 0; s < ns; ++s) {
-    const size_t rr = row0 + (size_t)s * L;
-    const float ms = wml[rr * 2];
-    if (ms == -INFINITY) continue;
-    const float wgt = expf(ms - M);
-    const f32x4 x = *reinterpret_cast<const f32x4*>(wacc + rr * D + c);
+  const float* wml = sp_ml<D>(a);
+  const size_t step = (size_t)Hq * L;  // rows from one range to the next
+  for (int u = blockIdx.x; u < a.s.B * Hq * upb; u += gridDim.x) {
+    const int bh = u / upb, b = bh / Hq, h = bh % Hq;
+    const int n = sp_ranges(p, sp_tiles(a, b));
+    if (n == 1) continue;  // uniform: already written out
+    int base = 0;
+    for (int b0 = lane; b0 < b; b0 += kWave) base += sp_ranges(p, sp_tiles(a, b0));
+    for (int x = 1; x < kWave; x <<= 1) base += __shfl_xor(base, x);
+    const int i = u % upb * RPB + threadIdx.x / TPR, c = (threadIdx.x % TPR) * 4;
+    if (i >= L) continue;  // (no barrier or exchange follows in this unit)
+    const size_t row0 = sp_row(a, base, h, i);
+    float M = -INFINITY;
+#pragma unroll 8
+    for (int s = 0; s < n; ++s) M = fmaxf(M, wml[(row0 + s * step) * 2]);
+    f32x4 num = {0.0f, 0.0f, 0.0f, 0.0f};
+    float den = 0.0f;
+#pragma unroll 4
+    for (int s = 0; s < n; ++s) {
+      const size_t rr = row0 + s * step;
+      const float ms = wml[rr * 2];
+      if (ms == -INFINITY) continue;  // every score of the range is -inf
+      const float wgt = expf(ms - M);
+      const f32x4 x = *reinterpret_cast<const f32x4*>(wacc + rr * D + c);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) num[e] += wgt * x[e];
-    den += wgt * wml[rr * 2 + 1];
+      for (int e = 0; e < 4; ++e) num[e] += wgt * x[e];
+      den += wgt * wml[rr * 2 + 1];
+    }
+    const float o[4] = {num[0] / den, num[1] / den, num[2] / den, num[3] / den};
+    store_out4<T>(a.out, (((size_t)b * L + i) * Hq + h) * D + c, o, a.s.out_f32);
   }
-  const float o[4] = {num[0] / den, num[1] / den, num[2] / den, num[3] / den};
-  store_out4<T>(a.out, (((size_t)b * L + i) * Hq + h) * D + c, o, a.s.out_f32);
 }
 
+// Ranges per request on average at most (the workspace and the grid hold
+// that many): about 2048 workgroups of ranges of at least 512 keys.
 int softmax_prefix_splits(const Shape& s, int max_prefix) {
   const long units = (long)s.B * s.Hkv;
   long want = units > 0 ? (2048 + units - 1) / units : 1;
@@ -607,25 +848,30 @@ size_t softmax_prefix_ws_bytes(const Shape& s, int n_split) {
 template <typename T, int D, bool PAGED>
 static hipError_t sp_go(const SoftmaxPrefixArgs& a, hipStream_t st) {
   const int ns = a.n_split;
-  int chunk = (a.max_prefix + a.s.L + ns - 1) / ns;
-  chunk = (chunk + kTile - 1) / kTile * kTile;
   const int G = a.s.Hq / a.s.Hkv;
-  const dim3 grid(a.s.B * a.s.Hkv * ns);
+  // Ranges the chip holds at once, per KV head: two workgroups per CU by
+  // their LDS, one with more than 4 waves, by their registers.
+  const int fill = max(1, (G > 4 ? 256 : 512) / a.s.Hkv);
+  // Ranges of a plan at most: three rounds, within the workspace, and at
+  // least what the longest range allows.
+  const int need = (int)(((long)a.max_prefix + a.s.L + kMaxRange - 1) / kMaxRange);
+  const int limit = min(a.s.B * ns, max(a.s.B * need, 3 * fill));
+  const dim3 grid(a.s.Hkv * limit);
   bool launched_ring = false;
   if constexpr (sizeof(T) == 2) {
     launched_ring = true;
     switch (G) {
-      case 1: hipLaunchKernelGGL((hyb_sp_ring_kernel<D, 1, PAGED>), grid, dim3(kWave), 0, st, a, chunk); break;
-      case 2: hipLaunchKernelGGL((hyb_sp_ring_kernel<D, 2, PAGED>), grid, dim3(kWave * 2), 0, st, a, chunk); break;
-      case 4: hipLaunchKernelGGL((hyb_sp_ring_kernel<D, 4, PAGED>), grid, dim3(kWave * 4), 0, st, a, chunk); break;
-      case 8: hipLaunchKernelGGL((hyb_sp_ring_kernel<D, 8, PAGED>), grid, dim3(kWave * 8), 0, st, a, chunk); break;
+      case 1: hipLaunchKernelGGL((hyb_sp_ring_kernel<D, 1, PAGED>), grid, dim3(kWave), 0, st, a, fill, limit); break;
+      case 2: hipLaunchKernelGGL((hyb_sp_ring_kernel<D, 2, PAGED>), grid, dim3(kWave * 2), 0, st, a, fill, limit); break;
+      case 4: hipLaunchKernelGGL((hyb_sp_ring_kernel<D, 4, PAGED>), grid, dim3(kWave * 4), 0, st, a, fill, limit); break;
+      case 8: hipLaunchKernelGGL((hyb_sp_ring_kernel<D, 8, PAGED>), grid, dim3(kWave * 8), 0, st, a, fill, limit); break;
       default: launched_ring = false;  // the register-staged kernel below
     }
   }
 #define HYB_SP_CASE(NG)                                                               \
   case NG:                                                                            \
     hipLaunchKernelGGL((hyb_sp_partial_kernel<T, D, NG, PAGED>), grid, dim3(kWave * NG), 0, st, a, \
-                       chunk);                                                        \
+                       fill, limit);                                                        \
     break;
   if (!launched_ring) {
     switch (G) {
@@ -643,12 +889,9 @@ static hipError_t sp_go(const SoftmaxPrefixArgs& a, hipStream_t st) {
 #undef HYB_SP_CASE
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || ns == 1) return e;  // one range: already written out
-  {
-    const size_t rows = (size_t)a.s.B * a.s.Hq * a.s.L;
-    constexpr int RPB = 256 / (D / 4);
-    hipLaunchKernelGGL((hyb_sp_combine_kernel<T, D>), dim3((unsigned)((rows + RPB - 1) / RPB)),
-                       dim3(256), 0, st, a);
-  }
+  const long units = (long)a.s.B * a.s.Hq * ((a.s.L + 1024 / D - 1) / (1024 / D));
+  hipLaunchKernelGGL((hyb_sp_combine_kernel<T, D>), dim3((unsigned)std::min<long>(units, 1024)), dim3(256), 0, st,
+                     a, fill, limit);
   return hipGetLastError();
 }
 

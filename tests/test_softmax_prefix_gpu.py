@@ -57,3 +57,45 @@ def test_no_prefix_equals_hybrid_with_empty_state():
                                                      out_f32=o32), ref, "bf16", "softmax P=0")
     check_outputs(lambda o32: hb.hybrid_attn_step(qd, kd, vd, act(Wt, "bf16"), f32(alpha), S, z,
                                                   out_f32=o32), ref, "bf16", "hybrid empty state")
+
+
+RANGES = [
+    # lengths far apart: the plan gives each request its own number of ranges,
+    # of whole tiles; (B, Hq, Hkv, d, L, dtype, Pmax, lengths or a seed)
+    (5, 8, 2, 128, 32, "bf16", 6016, [6016, 0, 31, 3000, 4097]),    # 4 heads per KV head
+    (3, 2, 2, 64, 9, "bf16", 3008, [3008, 1, 1600]),                # one wave per workgroup
+    (3, 4, 2, 128, 1, "bf16", 2080, [65, 2080, 1024]),
+    (2, 8, 1, 128, 32, "bf16", 4096, [4096, 700]),                  # 8 heads per KV head
+    (3, 6, 2, 64, 32, "bf16", 2048, [2048, 2017, 5]),               # register-staged kernel
+    (3, 4, 2, 64, 5, "f32", 2048, [2048, 1, 1500]),
+    # tiles per range around the copy ring's depth and its remainders
+    (7, 4, 1, 128, 32, "bf16", 544, [0, 32, 64, 96, 128, 160, 544]),
+    # more requests than the plan stages in LDS at once
+    (300, 4, 1, 64, 3, "bf16", 1088, 5),
+    (2100, 1, 1, 64, 2, "bf16", 544, 6),                            # a range per request at most
+]
+
+
+@pytest.mark.parametrize("case", RANGES, ids=lambda s: "x".join(map(str, s[:7])))
+def test_softmax_prefix_mixed_lengths(case):
+    B, Hq, Hkv, d, L, dt, Pmax, plens = case
+    dims = synth.Dims(B=B, Hq=Hq, Hkv=Hkv, d=d, L=L, F=32, dtype=dt)
+    announce(f"softmax_prefix ranges {case}")
+    if isinstance(plens, int):
+        plens = np.random.default_rng(plens).integers(0, Pmax + 1, B)
+    pl = np.array(plens, np.int32)
+    q, k, v = synth.block_qkv(dims, 91, 1.0)
+    kc, vc = synth.prefix_kv(B, Pmax, Hkv, d, 92, 1.0, dt)
+    kd, vd = act(kc, dt), act(vc, dt)
+    args = (act(q, dt), act(k, dt), act(v, dt))
+    ref = oracle.softmax_prefix(q, k, v, kc, vc, pl)
+    check_outputs(lambda o32: hb.softmax_prefix_step(*args, kd, vd, i32(pl), out_f32=o32), ref, dt,
+                  f"softmax_prefix ranges {case[:7]}")
+    # the paged cache follows the same plan: the same bits
+    pages = (B * Pmax // 32, 32, Hkv, d)
+    table = torch.arange(pages[0], dtype=torch.int32, device="cuda").view(B, -1)
+    a = hb.softmax_prefix_step(*args, kd, vd, i32(pl), out_f32=True)
+    b = hb.softmax_prefix_step_paged(*args, kd.view(pages), vd.view(pages), table, i32(pl),
+                                     out_f32=True)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
