@@ -116,9 +116,10 @@ struct SegPlan {
     return hi < end ? hi : end;
   }
 };
-// The prefill's plan (one round of walk workgroups over the chip, the
-// increments in about as many workgroups), and the backward's (the same).
+// The prefill's plans (with outputs, and without: pieces only), and the
+// backward's, which also sizes the prefill's workspace.
 SegPlan prefill_plan(const Shape& s, int T);
+SegPlan prefill_state_plan(const Shape& s, int T);
 SegPlan segment_plan(const Shape& s, int T);
 // The prefill's workspace, and the part the increments take under a plan.
 size_t prefill_ws_bytes(const Shape& s, int T);

@@ -8,15 +8,16 @@
 // the grid fills the chip (SegPlan).  A first launch (delta mode) computes the
 // state increments dS = sum_c phi(K_c)^T V_c and dz of the blocks of segments
 // 0 .. nseg-2, in pieces of a segment each or smaller, into the caller's
-// workspace; the second launch (walk mode) starts segment s from S + the
-// increments of the pieces before it and walks its blocks as below; the last
-// segment writes the final state.  Only the associativity of the sum is used,
-// so the result is the sequential one up to rounding order.  Without outputs,
-// only the last segment walks.
-// Ordering: with nseg > 1 the walk segments start from a snapshot of the
-// incoming S, z that a launch before the walk copies into the workspace, never
-// from S, z themselves, which the last segment overwrites in the same launch
-// (workgroups of one launch are not ordered).
+// workspace; a second (the scan) turns them into each segment's starting
+// state, S + the increments of the pieces before it; the third (walk mode)
+// walks each segment's blocks from there as below, and the last segment
+// writes the final state.  Only the associativity of the sum is used, so the
+// result is the sequential one up to rounding order.  Without outputs no
+// segment walks: the pieces cover the whole prompt and the scan adds them to
+// S.
+// Ordering: with nseg > 1 the walk segments start from what the scan left in
+// the workspace, never from S, z themselves, which the last segment
+// overwrites in the same launch (workgroups of one launch are not ordered).
 //
 // Within a segment, one workgroup per (request b, query head h) walks the
 // blocks in order, with the next block's Q, K and V in flight while the
@@ -63,32 +64,69 @@ struct PrefillCfg {
 };
 
 // Workspace layout (nseg > 1): the increments dS [units][npieces][D][f] and
-// dz [units][npieces][f], then the snapshot of the incoming state,
-// S0 [units][D][f] and z0 [units][f].
-__device__ inline const float* prefill_snapshot_S(const PrefillArgs& a, int npc, int u) {
-  const size_t f = 2 * (size_t)a.s.F, units = (size_t)a.s.B * a.s.Hq;
-  return a.ws + units * npc * (a.s.D * f + f) + (size_t)u * a.s.D * f;
+// dz [units][npieces][f], then the incoming state, S0 [units][D][f] and
+// z0 [units][f].  The scan replaces the increment of piece s * ppseg - 1 by
+// the starting state of segment s = 1 .. nseg-1.
+__device__ inline float* prefill_start_S(const PrefillArgs& a, const SegPlan& p, int u, int seg) {
+  const size_t f = 2 * (size_t)a.s.F, units = (size_t)a.s.B * a.s.Hq, npc = p.npieces();
+  const size_t at = seg > 0 ? (size_t)u * npc + seg * p.ppseg - 1 : 0;
+  return seg > 0 ? a.ws + at * a.s.D * f
+                 : a.ws + units * npc * (a.s.D * f + f) + (size_t)u * a.s.D * f;
 }
-__device__ inline const float* prefill_snapshot_z(const PrefillArgs& a, int npc, int u) {
-  const size_t f = 2 * (size_t)a.s.F, units = (size_t)a.s.B * a.s.Hq;
-  return a.ws + units * npc * (a.s.D * f + f) + units * a.s.D * f + (size_t)u * f;
+__device__ inline float* prefill_start_z(const PrefillArgs& a, const SegPlan& p, int u, int seg) {
+  const size_t f = 2 * (size_t)a.s.F, units = (size_t)a.s.B * a.s.Hq, npc = p.npieces();
+  const size_t at = seg > 0 ? (size_t)u * npc + seg * p.ppseg - 1 : 0;
+  return seg > 0 ? a.ws + units * npc * a.s.D * f + at * f
+                 : a.ws + units * npc * (a.s.D * f + f) + units * a.s.D * f + (size_t)u * f;
 }
 
-// Snapshot of the incoming state of every (request, head) unit into the
-// workspace, one workgroup per unit, 16-byte copies.  A unit whose slot is
-// out of range is skipped (its walk never reads the snapshot).
-__global__ __launch_bounds__(256) void hyb_prefill_snapshot_kernel(PrefillArgs a, int npc) {
-  const int u = blockIdx.x, Hq = a.s.Hq;
-  const int b = u / Hq, h = u % Hq;
+// The scan over the pieces of every (request, head) unit: a thread takes four
+// consecutive floats of the state (or of z) through all segments, so every
+// load of it is independent of the sums and several are in flight.  FINAL: no
+// segment walks; S, z + all pieces go back to S, z.  A unit whose slot is out
+// of range is skipped (its walk reads no starting state).
+// Bound by its bytes (64 KiB per unit, piece and segment at d = f = 128).  As
+// a pass of its own it costs 10 us at 8 x 8192 tokens (21 MB of increments),
+// where copying S and summing the pieces at each walk's start cost 12 us and
+// a chain of loads per segment; that chain kept a prompt to 8 segments.
+template <bool FINAL>
+__global__ __launch_bounds__(256) void hyb_prefill_scan_kernel(PrefillArgs a, SegPlan p) {
+  const int Hq = a.s.Hq;
+  const size_t f = 2 * (size_t)a.s.F, n = (size_t)a.s.D * f, per = (n + f) / 4;
+  const int wpu = (int)((per + blockDim.x - 1) / blockDim.x);  // workgroups per unit
+  const int u = blockIdx.x / wpu, b = u / Hq, h = u % Hq;
   const int slot = a.slots ? a.slots[b] : b;
   if (slot < 0 || slot >= a.s.n_slots) return;
-  const size_t f = 2 * (size_t)a.s.F, n = (size_t)a.s.D * f;
-  const size_t sbase = (size_t)slot * Hq + h;
-  const f32x4* src = reinterpret_cast<const f32x4*>(a.S + sbase * n);
-  f32x4* dst = reinterpret_cast<f32x4*>(const_cast<float*>(prefill_snapshot_S(a, npc, u)));
-  for (size_t i = threadIdx.x; i < n / 4; i += blockDim.x) dst[i] = src[i];
-  float* dz = const_cast<float*>(prefill_snapshot_z(a, npc, u));
-  for (size_t i = threadIdx.x; i < f; i += blockDim.x) dz[i] = a.z[sbase * f + i];
+  const size_t i = (size_t)(blockIdx.x % wpu) * blockDim.x + threadIdx.x;
+  if (i >= per) return;
+  const bool isz = i >= n / 4;
+  const size_t e = isz ? i * 4 - n : i * 4, len = isz ? f : n;
+  const size_t units = (size_t)a.s.B * Hq, npc = p.npieces(), sbase = (size_t)slot * Hq + h;
+  float* st = (isz ? a.z + sbase * f : a.S + sbase * n) + e;
+  float* inc = (isz ? a.ws + units * npc * n : a.ws) + (size_t)u * npc * len + e;
+  f32x4 acc = *reinterpret_cast<const f32x4*>(st);
+  if constexpr (FINAL) {
+#pragma unroll 8
+    for (int pc = 0; pc < p.npieces(); ++pc) acc += *reinterpret_cast<const f32x4*>(inc + pc * len);
+    *reinterpret_cast<f32x4*>(st) = acc;
+  } else {
+    *reinterpret_cast<f32x4*>((isz ? prefill_start_z(a, p, u, 0) : prefill_start_S(a, p, u, 0)) + e) = acc;
+    // (a piece is read before the start that replaces it is written)
+    constexpr int A = 8;  // pieces in flight
+    f32x4 x[A];
+    for (int p0 = 0; p0 < p.npieces(); p0 += A) {
+#pragma unroll
+      for (int j = 0; j < A; ++j)
+        x[j] = *reinterpret_cast<const f32x4*>(inc + min(p0 + j, p.npieces() - 1) * len);
+#pragma unroll
+      for (int j = 0; j < A; ++j) {
+        const int pc = p0 + j;
+        if (pc >= p.npieces()) break;
+        acc += x[j];
+        if ((pc + 1) % p.ppseg == 0) *reinterpret_cast<f32x4*>(inc + pc * len) = acc;
+      }
+    }
+  }
 }
 
 template <typename T, int D, int F>
@@ -113,14 +151,13 @@ __global__ __launch_bounds__(kWave*(D / kTile)) void hyb_prefill_kernel(
   const int u = vix % units, seg = vix / units;
   const int b = u / Hq, h = u % Hq, g = h / (Hq / Hkv);
   const int slot = a.slots ? a.slots[b] : b;
-  const bool want_out = !delta && a.out != nullptr;
+  const bool want_out = !delta && a.out != nullptr;  // (no outputs: nseg = 1)
   const bool last = !delta && seg == nseg - 1;
   const size_t qstride = (size_t)Hq * D, kstride = (size_t)Hkv * D;
   const int col = w * kTile + li;
   const int nblk = T_ / L;
   const int blk0 = delta ? p.piece_lo(seg) : seg * p.sb;
   const int blk1 = min(nblk, delta ? p.piece_hi(seg) : blk0 + p.sb);
-  if (!delta && !want_out && !last) return;  // state only: the last segment walks
   if (slot < 0 || slot >= a.s.n_slots) {  // uniform per workgroup
     if (want_out) {
       const size_t ob = ((size_t)b * T_ * Hq + h) * D;
@@ -138,37 +175,27 @@ __global__ __launch_bounds__(kWave*(D / kTile)) void hyb_prefill_kernel(
   // [units][npieces][f].
   float* __restrict__ wsS = a.ws + (size_t)u * npc * D * f;
   float* __restrict__ wsz = a.ws + (size_t)units * npc * D * f + (size_t)u * npc * f;
-  // (without outputs only the last segment walks, and no snapshot is taken)
-  const bool snap = nseg > 1 && a.out != nullptr;
-  const float* __restrict__ S0 = snap ? prefill_snapshot_S(a, npc, u) : Sh;
-  const float* __restrict__ z0 = snap ? prefill_snapshot_z(a, npc, u) : zh;
+  const float* __restrict__ S0 = nseg > 1 ? prefill_start_S(a, p, u, seg) : Sh;
+  const float* __restrict__ z0 = nseg > 1 ? prefill_start_z(a, p, u, seg) : zh;
 
-  // Starting state: zero for a delta, else S plus the earlier segments'
-  // increments, all in the accumulator layout.
+  // Starting state: zero for a delta, else the segment's, in the accumulator
+  // layout.
   f32x16 sacc[C::NRT];
-  auto add_state = [&](const float* src, bool first) {
-#pragma unroll
-    for (int rt = 0; rt < C::NRT; ++rt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {  // rows rt*32 + j*8 + hh*4 .. +3: 16 bytes
-        const f32x4 x = *reinterpret_cast<const f32x4*>(
-            src + (size_t)col * f + rt * kTile + row_of(4 * j, hh));
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sacc[rt][4 * j + r] = first ? x[r] : sacc[rt][4 * j + r] + x[r];
-      }
-  };
   if (delta) {
 #pragma unroll
     for (int rt = 0; rt < C::NRT; ++rt) sacc[rt] = f32x16{};
     for (int r = tid; r < f; r += blockDim.x) sh.z[r] = 0.0f;
   } else {
-    add_state(S0, true);
-    for (int s = 0; s < seg * p.ppseg; ++s) add_state(wsS + (size_t)s * D * f, false);
-    for (int r = tid; r < f; r += blockDim.x) {
-      float zr = z0[r];
-      for (int s = 0; s < seg * p.ppseg; ++s) zr += wsz[(size_t)s * f + r];
-      sh.z[r] = zr;
-    }
+#pragma unroll
+    for (int rt = 0; rt < C::NRT; ++rt)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {  // rows rt*32 + j*8 + hh*4 .. +3: 16 bytes
+        const f32x4 x = *reinterpret_cast<const f32x4*>(
+            S0 + (size_t)col * f + rt * kTile + row_of(4 * j, hh));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sacc[rt][4 * j + r] = x[r];
+      }
+    for (int r = tid; r < f; r += blockDim.x) sh.z[r] = z0[r];
   }
 
   const T* __restrict__ Wt_h = (const T*)a.W + (size_t)h * F * D;
@@ -455,7 +482,7 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int li = lane & 31, hh = lane >> 5;
   const int Hq = a.s.Hq, Hkv = a.s.Hkv, L = a.s.L, T_ = a.T;
-  const int units = a.s.B * Hq, nseg = p.nseg, npc = p.npieces();
+  const int units = a.s.B * Hq, nseg = p.nseg;
   const int vix = xcd_unit(blockIdx.x, units * nseg);
   const int u = vix % units, seg = vix / units;
   const int b = u / Hq, h = u % Hq, g = h / (Hq / Hkv);
@@ -503,15 +530,10 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
     for (int ks = 0; ks < C::KD; ++ks) o[ks] = buf_op<T>(krs, klane + ks * KW * (int)sizeof(T), so);
   };
 
-  // Set-up: z + the earlier segments' increments into z[0].
+  // Set-up: the segment's starting z into z[0].
   {
-    const float* __restrict__ wsz = a.ws + (size_t)units * npc * D * f + (size_t)u * npc * f;
-    const float* __restrict__ z0 = nseg > 1 ? prefill_snapshot_z(a, npc, u) : a.z + ((size_t)slot * Hq + h) * f;
-    for (int r = tid; r < f; r += C::NWAVE * kWave) {
-      float zr = z0[r];
-      for (int s = 0; s < seg * p.ppseg; ++s) zr += wsz[(size_t)s * f + r];
-      sh.z[0][r] = zr;
-    }
+    const float* __restrict__ z0 = nseg > 1 ? prefill_start_z(a, p, u, seg) : a.z + ((size_t)slot * Hq + h) * f;
+    for (int r = tid; r < f; r += C::NWAVE * kWave) sh.z[0][r] = z0[r];
   }
   lds_barrier();  // z ready
 
@@ -784,9 +806,8 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
     const int col = cw * kTile + li;
     const size_t sbase = (size_t)slot * Hq + h;
     float* __restrict__ Sh = a.S + sbase * f * D;
-    const float* __restrict__ wsS = a.ws + (size_t)u * npc * D * f;
-    const float* __restrict__ S0 = nseg > 1 ? prefill_snapshot_S(a, npc, u) : Sh;
-    // S columns col of all f rows: S + the earlier segments' increments.
+    const float* __restrict__ S0 = nseg > 1 ? prefill_start_S(a, p, u, seg) : Sh;
+    // S columns col of all f rows, the segment's starting state.
     // (Declared here, not before the role branches: a value live across the
     // other roles' code takes registers there too.)
     f32x16 sacc[C::NRT];
@@ -798,20 +819,6 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
 #pragma unroll
         for (int r = 0; r < 4; ++r) sacc[rt][4 * j + r] = x[r];
       }
-    for (int s = 0; s < seg * p.ppseg; ++s) {
-#pragma unroll
-      for (int rt = 0; rt < C::NRT; ++rt) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const f32x4 y = *reinterpret_cast<const f32x4*>(
-              wsS + (size_t)s * D * f + (size_t)col * f + rt * kTile + row_of(4 * j, hh));
-#pragma unroll
-          for (int r = 0; r < 4; ++r) sacc[rt][4 * j + r] += y[r];
-        }
-        // (one row tile of the increment in flight at a time)
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
     // V rows of this wave's 32 columns, one block ahead: 4 lanes per row
     // (16 bytes each), 16 rows per load; a row at or past the block length
     // reads the next rows of the request (zero past its end) and is zeroed
@@ -1312,18 +1319,20 @@ static hipError_t prefill_delta_go(const PrefillArgs& a, const SegPlan& p, hipSt
 template <typename T, int D, int F>
 static hipError_t prefill_go(const PrefillArgs& a, hipStream_t st) {
   const int units = a.s.B * a.s.Hq;
-  const SegPlan p = prefill_plan(a.s, a.T);
+  const bool state_only = a.out == nullptr;
+  const SegPlan p = state_only ? prefill_state_plan(a.s, a.T) : prefill_plan(a.s, a.T);
   const dim3 block(kWave * (D / kTile));
   if (p.nseg > 1) {
-    // only the last segment walks when no outputs are wanted, and it alone
-    // writes the state: no snapshot is needed then
-    if (a.out != nullptr) {
-      hipLaunchKernelGGL(hyb_prefill_snapshot_kernel, dim3(units), dim3(256), 0, st, a, p.npieces());
-      const hipError_t e0 = hipGetLastError();
-      if (e0 != hipSuccess) return e0;
-    }
     const hipError_t e = prefill_delta_go<T, D, F>(a, p, st);
     if (e != hipSuccess) return e;
+    const size_t per = (size_t)(D + 1) * 2 * F / 4;  // threads per unit
+    const dim3 grid((unsigned)(units * ((per + 255) / 256)));
+    if (state_only)
+      hipLaunchKernelGGL(hyb_prefill_scan_kernel<true>, grid, dim3(256), 0, st, a, p);
+    else
+      hipLaunchKernelGGL(hyb_prefill_scan_kernel<false>, grid, dim3(256), 0, st, a, p);
+    const hipError_t e0 = hipGetLastError();
+    if (e0 != hipSuccess || state_only) return e0;
   }
   // The pipelined walk serves bf16 with F <= 64 when outputs are wanted;
   // the single-group walk serves the rest.
@@ -1371,13 +1380,15 @@ hipError_t launch_prefill_delta(const PrefillArgs& a, const SegPlan& p, hipStrea
 }
 
 
-// The prefill's plan.  A walk workgroup takes a whole CU (its LDS), so the
-// walk takes about one workgroup per CU (256 CUs): segments are what the
-// batch's (request, head) units leave to fill; at most 8 segments and at
-// least 4 blocks per segment.  The increments of segments 0 .. nseg-2 are cut
-// into pieces so that they too take about one workgroup per CU, with at
-// least 2 blocks per piece (the increment kernel takes blocks in pairs).
-SegPlan prefill_plan(const Shape& s, int T) {
+// One round of walk workgroups: a walk workgroup takes a whole CU (its LDS),
+// so segments are what the batch's (request, head) units leave of 256 CUs to
+// fill; at most 8 segments and at least 4 blocks per segment.  The increments
+// of segments 0 .. nseg-2 are cut into pieces so that they too take about one
+// workgroup per CU, with at least 2 blocks per piece (the increment kernel
+// takes blocks in pairs).  The backward's walks use this plan as it is (they
+// sum the pieces before or after their segment at their start); the prefill's
+// workspace is sized by it.
+SegPlan segment_plan(const Shape& s, int T) {
   constexpr int kCUs = 256;
   const int units = s.B * s.Hq, nblk = T / s.L;
   int nseg = (kCUs + units - 1) / units;
@@ -1404,11 +1415,65 @@ SegPlan prefill_plan(const Shape& s, int T) {
   return p;
 }
 
-// The backward's walks use the prefill's plan: the same one round of walk
-// workgroups (a walk workgroup takes a whole CU, and a second round would
-// only repeat each workgroup's start, the sum of the earlier increments) and
-// the same increment pieces.
-SegPlan segment_plan(const Shape& s, int T) { return prefill_plan(s, T); }
+// Workgroups of the walk and of the increments that the chip holds at once:
+// one per CU of the pipelined kernels (their LDS), two of the single-group
+// kernel, four at d = 64 (their registers).
+static int prefill_fill(const Shape& s) {
+  if (s.dtype == 1 && s.F <= 64) return 256;
+  return s.D == 64 ? 1024 : 512;
+}
+
+// The prefill's plan: the (segments, pieces per segment) with the least
+// estimated time among those whose pieces fit the workspace of segment_plan.
+// In walk steps: rounds of walk workgroups times a segment's blocks and its
+// start (about 4); rounds of increment workgroups times a piece's blocks, at
+// 0.45 of a step each, and their start (about 2); and the two launches (4).
+// With up to 8 segments, as the backward's, one prompt of 16384 tokens walks
+// on 128 CUs: 240 us, against 126 us with the 16 segments chosen here (2 of
+// 8192: 162 and 125, 4 of 2048: 99 and 79, 1 of 1024: 66 and 35).
+SegPlan prefill_plan(const Shape& s, int T) {
+  const int units = s.B * s.Hq, nblk = T / s.L, room = segment_plan(s, T).npieces();
+  const int fill = prefill_fill(s);
+  SegPlan best;
+  best.sb = best.pb = nblk;
+  float least = (float)((units + fill - 1) / fill) * (nblk + 4);
+  SegPlan p;
+  for (p.nseg = 2; p.nseg <= room + 1 && p.nseg <= nblk; ++p.nseg) {
+    p.sb = (nblk + p.nseg - 1) / p.nseg;
+    if ((p.nseg - 1) * p.sb >= nblk) continue;  // the last segment non-empty
+    for (p.ppseg = 1; p.npieces() <= room && p.ppseg <= p.sb; ++p.ppseg) {
+      p.pb = (p.sb + p.ppseg - 1) / p.ppseg;
+      if ((p.ppseg - 1) * p.pb >= p.sb) continue;  // every piece non-empty
+      const long wg = (long)units * p.nseg, dg = (long)units * p.npieces();
+      const float cost = (float)((wg + fill - 1) / fill) * (float)(p.sb + 4) +
+                         (float)((dg + fill - 1) / fill) * (0.45f * (float)p.pb + 2.0f) + 4.0f;
+      if (cost < least) {
+        least = cost;
+        best = p;
+      }
+    }
+  }
+  return best;
+}
+
+// The plan without outputs: pieces over the whole prompt (segments 0 ..
+// nseg-2 of a plan whose last segment is empty), as many as fit the workspace
+// and the chip in one round, of at least 2 blocks; nseg = 1 (one walk per
+// unit) where there is no workspace.  16384 tokens: 42 us, against 297 us
+// when the last segment still walked, on the unit's one workgroup (8 prompts
+// of 8192: 138 and 476).
+SegPlan prefill_state_plan(const Shape& s, int T) {
+  const int units = s.B * s.Hq, nblk = T / s.L, room = segment_plan(s, T).npieces();
+  SegPlan p;
+  p.sb = p.pb = nblk;
+  if (room < 1) return p;
+  int n = prefill_fill(s) / units;
+  n = n > room ? room : n;
+  n = n < 1 ? 1 : n;
+  p.sb = p.pb = (nblk + n - 1) / n < 2 ? 2 : (nblk + n - 1) / n;
+  p.nseg = (nblk + p.sb - 1) / p.sb + 1;
+  return p;
+}
 
 size_t prefill_delta_ws_bytes(const Shape& s, const SegPlan& p) {
   if (p.npieces() <= 0) return 0;
@@ -1417,10 +1482,10 @@ size_t prefill_delta_ws_bytes(const Shape& s, const SegPlan& p) {
 }
 
 size_t prefill_ws_bytes(const Shape& s, int T) {
-  const SegPlan p = prefill_plan(s, T);
+  const SegPlan p = segment_plan(s, T);
   if (p.nseg <= 1) return 0;
   const size_t f = 2 * (size_t)s.F;
-  // the increments, then the snapshot of the incoming state
+  // the increments, then the incoming state
   return prefill_delta_ws_bytes(s, p) + (size_t)s.B * s.Hq * ((size_t)s.D * f + f) * 4;
 }
 

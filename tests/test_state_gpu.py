@@ -204,3 +204,57 @@ def test_prefill_segments(shape):
     torch.cuda.synchronize()
     assert_state_delta(state_host(S2), host(z2), c0["S"], c0["z"], Sr, zr, dt,
                        f"prefill segments state-only {shape}")
+
+
+PLAN_CASES = [
+    # (B, Hq, Hkv, d, L, F, dtype, nblk): segments and pieces as the plan
+    # chooses them -- many segments of one unit (more pieces than the scan
+    # keeps in flight), several pieces per segment, the last segment short,
+    # the fewest blocks that are cut, and the single-group kernel (fp32, F = 128)
+    (1, 2, 1, 64, 8, 32, "bf16", 203),
+    (1, 1, 1, 64, 4, 32, "f32", 130),
+    (5, 4, 2, 128, 32, 64, "bf16", 65),
+    (12, 16, 4, 64, 16, 32, "bf16", 17),
+    (2, 16, 4, 128, 32, 128, "bf16", 24),
+    (1, 16, 4, 128, 5, 64, "bf16", 8),
+    (2, 4, 2, 128, 32, 64, "f32", 19),
+]
+
+
+@pytest.mark.parametrize("shape", PLAN_CASES, ids=lambda s: "x".join(map(str, s)))
+def test_prefill_plans(shape):
+    """Segments, pieces and the scan of the plan's choice, through slots (the
+    last request's out of range where there are several), with outputs and
+    state-only, from a workspace of NaN bytes."""
+    B, Hq, Hkv, d, L, F, dt, nblk = shape
+    dims = synth.Dims(B=B, Hq=Hq, Hkv=Hkv, d=d, L=L, F=F, dtype=dt)
+    T = nblk * L
+    announce(f"prefill plans {shape}")
+    q, k, v = synth.block_qkv(dims.with_(L=T), 191, 1.0)
+    Wt, alpha = synth.feature_weights(dims, 192, 193, 1.0 / np.sqrt(d))
+    c0 = make_case(dims, 16, seed=194, peaky=True)
+    n = B - 1 if B > 1 else B                      # requests with a slot
+    at = np.arange(B)[::-1] + 1                    # slots, scattered over B + 1 rows
+    slots = np.where(np.arange(B) < n, at, B + 1).astype(np.int32)
+    S0 = np.zeros((B + 1, Hq, 2 * F, d), np.float32)
+    z0 = np.zeros((B + 1, Hq, 2 * F), np.float32)
+    S0[at], z0[at] = c0["S"], c0["z"]
+    o_r, Sr, zr = oracle.prefill(q[:n], k[:n], v[:n], Wt, alpha, c0["S"][:n], c0["z"][:n], L)
+    hd = hb.make_dims(B, Hq, Hkv, d, L, 2 * F, hb.HYB_BF16 if dt == "bf16" else hb.HYB_F32, B + 1)
+    need = hb.workspace_bytes(hd, hb.OP_PREFILL, T)
+    ins = (act(q, dt), act(k, dt), act(v, dt), act(Wt, dt), f32(alpha))
+    for want_out in (True, False):
+        S, z = state_dev(S0), f32(z0)
+        ws = torch.full((max(need, 16),), 0xFF, dtype=torch.uint8, device="cuda")
+        out = hb.hybrid_state_prefill(*ins, S, z, L, slots=i32(slots), want_out=want_out,
+                                      out_f32=True, ws=ws)
+        torch.cuda.synchronize()
+        if want_out:
+            assert_close(host(out[:n]), o_r, dt, f"prefill plans out {shape}")
+            assert torch.isnan(out[n:]).all()
+        Sh, zh = state_host(S), host(z)
+        assert_state_delta(Sh[at[:n]], zh[at[:n]], S0[at[:n]], z0[at[:n]], Sr, zr, dt,
+                           f"prefill plans {shape}")
+        rest = np.setdiff1d(np.arange(B + 1), at[:n])
+        assert np.array_equal(Sh[rest], S0[rest].astype(np.float64))
+        assert np.array_equal(zh[rest], z0[rest].astype(np.float64))
