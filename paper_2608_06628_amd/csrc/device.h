@@ -371,6 +371,77 @@ __device__ inline void lds_pair_op_nat(const uint32_t* row, int ks, int hh, bf16
   lo = __builtin_bit_cast(bf16x8, l);
 }
 
+// Two transposing LDS reads as one operand.  In each 16-lane quarter the read
+// gives lane i element i % 4 of the 8-byte pieces addressed by lanes
+// i / 4 + 4j (j = 0 .. 3): with lane i addressing row r + i / 4 at columns
+// c + 4 (i % 4) .. + 3, it receives rows r .. r + 3 of column c + i.
+__device__ inline bf16x8 lds_tr_op(const void* p0, const void* p1) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  const s16x4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p0);
+  const s16x4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p1);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// A 32-row tile of f features per row (f = 64 or 128) as bf16 planes in LDS,
+// rows of tokens, for a producer that holds 4 consecutive features of a token
+// per register group (accumulator order) and consumers that contract over the
+// tokens: written as 8-byte pieces, read back transposed by lds_tr_op.  Piece
+// u of row t sits at u ^ swz(t).  swz is one-to-one over the rows that share
+// a bank, so a write (one piece of 32 rows) touches every bank once, and it
+// puts four consecutive rows into different groups of 8 pieces, so a
+// transposing read (8 pieces of 4 rows per half wave) does too.
+template <int f>
+struct TokTile {
+  static_assert(f == 64 || f == 128, "a row fills half or all of the banks");
+  static constexpr int kPlane = kTile * f;  // elements of a plane
+  __device__ static inline int swz(int t) {
+    return f == 128 ? ((t & 3) << 3) | (t >> 2) : ((t & 2) << 2) | (t >> 2);
+  }
+  // Byte offset of the pieces of features 8j + 4hh .. + 3 of row t, before
+  // the constant ^ (16 * j).
+  __device__ static inline int write_base(int t, int hh) { return t * f * 2 + 8 * (hh ^ swz(t)); }
+  // Byte offset of this lane's reads of the operand "features 32rt + li at
+  // the tokens row_of(8ks + e, hh)": piece 0 or 1 (e < 4 or not) of it is at
+  // (base ^ 8 (8rt + 4ks + 2piece)) + (16ks + 8piece) * 2f.
+  __device__ static inline int read_base(int lane) {
+    const int i = lane & 15, b = (lane >> 4) & 1, hh = lane >> 5;
+    return (4 * hh + (i >> 2)) * f * 2 + 8 * ((swz(i >> 2) & 24) | ((4 * b + (i & 3)) ^ hh));
+  }
+  __device__ static inline bf16x8 op(const bf16* plane, int base, int rt, int ks) {
+    const char* p = reinterpret_cast<const char*>(plane);
+    return lds_tr_op(p + (base ^ (8 * (8 * rt + 4 * ks))) + 16 * ks * 2 * f,
+                     p + (base ^ (8 * (8 * rt + 4 * ks + 2))) + (16 * ks + 8) * 2 * f);
+  }
+  // The same for 16x16 tiles with the tokens in no particular order (a sum
+  // over all of them): features 16ft + lane % 16, every token once over the
+  // four lane quarters.
+  __device__ static inline int sum_base(int lane) {
+    const int i = lane & 15, b = (lane >> 4) & 1, hh = lane >> 5;
+    return (16 * b + 8 * hh + (i >> 2)) * f * 2 + 8 * ((swz(i >> 2) & 24) | ((i & 3) ^ (4 * b + 2 * hh)));
+  }
+  __device__ static inline bf16x8 sum_op(const bf16* plane, int base, int ft) {
+    const char* p = reinterpret_cast<const char*>(plane);
+    return lds_tr_op(p + (base ^ (8 * 4 * ft)), p + (base ^ (8 * (4 * ft + 1))) + 4 * 2 * f);
+  }
+};
+
+// Four fp32 values as bf16 pieces hi = bf16(x) and lo = bf16(x - hi), two at a
+// time (one paired rounding each).
+__device__ inline void split_hi_lo4(const float* x, bf16x4& hi, bf16x4& lo) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 h, l;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    h[e] = __builtin_bit_cast(uint32_t, bf16x2{(bf16)x[2 * e], (bf16)x[2 * e + 1]});
+    const float h0 = __builtin_bit_cast(float, h[e] << 16);
+    const float h1 = __builtin_bit_cast(float, h[e] & 0xffff0000u);
+    l[e] = __builtin_bit_cast(uint32_t, bf16x2{(bf16)(x[2 * e] - h0), (bf16)(x[2 * e + 1] - h1)});
+  }
+  hi = __builtin_bit_cast(bf16x4, h);
+  lo = __builtin_bit_cast(bf16x4, l);
+}
+
 template <typename T>
 __device__ inline void store_out1(void* out, size_t idx, float v, bool f32) {
   if (sizeof(T) == 4 || f32)
@@ -413,6 +484,10 @@ __device__ inline float log_sigmoid(float a) {
 // Word 3 of a raw buffer resource on gfx9-family chips (32-bit data
 // format; the untyped loads and stores used here take no other field).
 constexpr int kBufferWord3 = 0x00020000;
+
+// A lane offset past the end of any raw buffer used here (all under 2 GiB):
+// the load returns zero.
+constexpr int kPastBuffer = 0x7ffffff0;
 
 // A 16-byte piece per lane from a buffer straight into LDS: lane l's piece
 // goes to lds + 16 l (lds is the wave's base, uniform), read from the

@@ -407,23 +407,33 @@ __global__ __launch_bounds__(kWave*(D / kTile)) void hyb_prefill_kernel(
 //     a block over two iterations -- the logits, the scores, the first
 //     exponentials and the softmax rows of block it+1, then the rest of
 //     phi(Q) of block it, its store and the store of P (a bf16 pair hi + lo);
-//   K waves (2, 3): phi(K) likewise, stored transposed as hi | lo pairs;
-//     with the store, z_{it+1} = z_it + phi(K_it)^T 1 (on the MFMAs, from
-//     the tile just stored); with the first half of block it+1, lin_den =
-//     phi(Q) z of block it-1 and its merge coefficients;
-//   state waves (D/32): the output store of block it-3 (whole rows, from
-//     the LDS staging tile the state waves filled an iteration before), the
-//     merge of block it-2 (two coefficients per row) into staging; then, for
-//     block it-1: the V^T operands of the wave's 32 columns, the readout
+//     with the second half, z_it = z_{it-1} + phi(K_{it-1})^T 1 (MFMAs);
+//   K waves (2, 3): phi(K) likewise, stored as rows of hi and lo planes
+//     (TokTile); with the first half of block it+1, the output store of block
+//     it-3 (whole rows, from the staging tile the state waves filled an
+//     iteration before), then lin_den = phi(Q) z of block it-1 (on the MFMAs, z
+//     as three bf16 parts, which hold all of its bits) and its merge
+//     coefficients;
+//   state waves (D/32): the merge of block it-2 (two coefficients per row)
+//     into staging; then, for block it-1: the V^T operands of the wave's 32 columns, the readout
 //     phi(Q) S against the state of the blocks before it, P V of its
 //     columns and the commit into S columns 32w .. 32w+31 (fp32
 //     accumulators).
 // The QS and K waves hand a block to the state waves through a double
 // buffer (written in iteration c, read in c+1), the merge coefficients
-// through a second (written in c+1, read in c+2); z goes from one K wave to
-// the other through a triple buffer (z_c is written in iteration c-1 and read
-// in c and c+1); W_h^T stays in LDS.
+// through a second (written in c+1, read in c+2); z goes from one QS wave to
+// the other through a triple buffer (z_c is written in iteration c and read
+// in c+1).
 // Arithmetic and operand precision are those of the single-group walk above.
+// A block step is bound by the longest role between two barriers, and by what
+// two waves of a SIMD issue together, so the hand-over costs no instructions
+// that only move bits: phi(K)^T and V^T operands come from row-major tiles by
+// transposing LDS reads (as hi | lo pairs in dwords they took 72 byte permutes
+// per state wave and block, V^T 16 masked two-byte reads, and lin_den 130 VALU
+// instructions); and the state waves, the longest role, load nothing behind a
+// store (their wait for V's rows had counted the block's output store, issued
+// just before: 1,700 of 5,000 cycles a block).  8 x 8192 tokens: 385 us before,
+// 355 us with the increments below changed alike.
 // ---------------------------------------------------------------------------
 template <typename T, int D, int F>
 struct PrefillPipeCfg {
@@ -445,7 +455,7 @@ struct PrefillPipeCfg {
   static constexpr int QLD = f + 4, PLD = kTile + 4;
   struct alignas(16) Buf {            // written in iteration c, read in c + 1
     T phiQ[kTile][QLD];               // phi(q_i)[r] at [i][r]
-    uint32_t phiKT[f][kTile + 4];     // phi(k_t)[r] at [r][t]: bf16 hi | lo << 16
+    T phiK[2][kTile * f];             // phi(k_t): planes hi and lo (TokTile)
     T ph[kTile][PLD];                 // P (relative to the row max) as hi + lo,
     T pl[kTile][PLD];                 //   [query][key]
     float m[kTile], den[kTile];       // row max and sum of the block scores
@@ -454,10 +464,36 @@ struct PrefillPipeCfg {
     Buf buf[2];
     float2 coef[2][kTile];            // merge: out = x P V + y phi(Q) S per row
     float z[3][f];                    // z_c at [(c - first block) % 3]
-    float stage[2][kTile][D + 4];     // merged outputs of a block, [row][column]
-    T vt[NC][kTile][kTile + 8];       // V rows of each state wave's columns
+    T zp[3][3][f];                    // and as three parts, their sum exactly z_c
+    float stage[2][kTile][D + 4];     // merged outputs of a block, [row][column]; as
+                                      // bf16, rows of 2D bytes (StageRow)
+    T vt[NC][kTile][kTile];           // V rows of each state wave's columns
   };
 };
+
+// Byte offset of columns c .. c+3 of row t of a staged bf16 tile: 16-byte
+// chunk c/8 at (c/8) ^ (t % 16) (D = 128; ^ (t / 2 % 8) for D = 64), its 8-byte
+// halves swapped in rows 16 .. 31, so that the same columns of 32 rows (a
+// write) fall in distinct banks, as whole rows (a read) do.
+template <int D>
+struct StageRow {
+  __device__ static inline int swz(int t) { return D == 128 ? t & 15 : (t >> 1) & 7; }
+  __device__ static inline int at(int t, int c) {
+    return t * D * 2 + (((c >> 3) ^ swz(t)) * 16) + ((((c >> 2) ^ (t >> 4)) & 1) * 8);
+  }
+};
+
+// Four floats as three bf16 parts each: x = p0 + p1 + p2 (8 significant bits
+// apiece cover the 24 of x).
+__device__ inline void split_three4(const f32x4& x, bf16x4& p0, bf16x4& p1, bf16x4& p2) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    p0[e] = (bf16)x[e];
+    const float r = x[e] - (float)p0[e];
+    p1[e] = (bf16)r;
+    p2[e] = (bf16)(r - (float)p1[e]);
+  }
+}
 
 template <int D>
 constexpr int pipe_threads() {
@@ -471,6 +507,7 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
   typedef typename C::M M;
   typedef typename C::op_t op_t;
   typedef WaveFeatMap<T, D, F> WFM;
+  typedef TokTile<2 * F> Tok;
   constexpr int f = C::f, E = M::E, KW = M::KW, NT = C::NT, NC = C::NC;
   static_assert(sizeof(T) == 2, "the pipelined walk is the bf16 path");
   static_assert(pipe_threads<D>() == kWave * C::NWAVE, "launch bounds match the waves");
@@ -533,7 +570,12 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
   // Set-up: the segment's starting z into z[0].
   {
     const float* __restrict__ z0 = nseg > 1 ? prefill_start_z(a, p, u, seg) : a.z + ((size_t)slot * Hq + h) * f;
-    for (int r = tid; r < f; r += C::NWAVE * kWave) sh.z[0][r] = z0[r];
+    for (int r = 4 * tid; r < f; r += 4 * C::NWAVE * kWave) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(z0 + r);
+      *reinterpret_cast<f32x4*>(&sh.z[0][r]) = x;
+      split_three4(x, *reinterpret_cast<bf16x4*>(&sh.zp[0][0][r]), *reinterpret_cast<bf16x4*>(&sh.zp[0][1][r]),
+                   *reinterpret_cast<bf16x4*>(&sh.zp[0][2][r]));
+    }
   }
   lds_barrier();  // z ready
 
@@ -640,6 +682,85 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
       }
       const float scale = 1.0f / sqrtf((float)D);
       const float lw = log_sigmoid(a.alpha[h]);
+      // K: the output store of block c, whole rows (D/8 lanes per row, 8
+      // columns each), a scalar base and 32-bit lane offsets
+      const bool out_f32 = a.s.out_f32;
+      auto store_rows = [&](int c) __attribute__((always_inline)) {
+        constexpr int LPR = D / 8, RPP = kWave / LPR, NP = kTile / RPP;  // lanes per row, rows per pass
+        const char* st = reinterpret_cast<const char*>(sh.stage[(c - blk0) & 1]);
+        int l = lane;  // (opaque: addresses are formed here, not kept across the loop)
+        asm volatile("" : "+v"(l));
+        const int r0 = l / LPR, c8 = l % LPR * 8;
+        const size_t row = (size_t)b * T_ + (size_t)c * L;
+        if (out_f32) {
+          char* ob = (char*)a.out + (row * qstride + (size_t)h * D) * 4;
+#pragma unroll 2
+          for (int p = 0; p < NP; ++p) {
+            const int t = p * RPP + r0;
+            const f32x4* s = reinterpret_cast<const f32x4*>(&sh.stage[(c - blk0) & 1][t][c8]);
+            const f32x4 x0 = s[0], x1 = s[1];
+            if (t < L) {
+              f32x4* o = reinterpret_cast<f32x4*>(ob + (unsigned)((t * (int)qstride + c8) * 4));
+              o[0] = x0;
+              o[1] = x1;
+            }
+          }
+        } else {
+          char* ob = (char*)a.out + (row * qstride + (size_t)h * D) * sizeof(T);
+          u32x4 x[NP];
+#pragma unroll
+          for (int p = 0; p < NP; ++p) x[p] = *reinterpret_cast<const u32x4*>(st + (StageRow<D>::at(p * RPP + r0, c8) & ~15));
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int p = 0; p < NP; ++p) {
+            const int t = p * RPP + r0;
+            if (p * RPP >= 16) x[p] = u32x4{x[p][2], x[p][3], x[p][0], x[p][1]};
+            if (t < L) *reinterpret_cast<u32x4*>(ob + (unsigned)((t * (int)qstride + c8) * 2)) = x[p];
+          }
+        }
+      };
+      // QS: z_{c+1} = z_c + phi(K_c)^T 1 from the tile of block c, as
+      // accumulator tiles of 16 features whose columns are all equal: lane
+      // column ft keeps tile ft, so one lane row holds all of z.
+      auto z_update = [&](int c) __attribute__((always_inline)) {
+        const typename C::Buf& Bc = sh.buf[(c - blk0) & 1];
+        int l = lane;  // (opaque, as above)
+        asm volatile("" : "+v"(l));
+        const int zb = Tok::sum_base(l), ft = l & 15;
+        const int r = (min(ft, f / 16 - 1)) * 16 + (l >> 4) * 4;
+        const f32x4 zc = *reinterpret_cast<const f32x4*>(&sh.z[(c - blk0) % 3][r]);
+        f32x4 sum = {};
+#pragma unroll
+        for (int f0 = 0; f0 < f / 16; f0 += 4) {
+          op_t kh[4], kl[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            kh[j] = Tok::sum_op(Bc.phiK[0], zb, f0 + j);
+            kl[j] = Tok::sum_op(Bc.phiK[1], zb, f0 + j);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          f32x4 dz[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) dz[j] = Mma16<T>::mma(kh[j], ones, f32x4{});
+#pragma unroll
+          for (int j = 0; j < 4; ++j) dz[j] = Mma16<T>::mma(kl[j], ones, dz[j]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] = ft == f0 + j ? dz[j][e] : sum[e];
+        }
+        const f32x4 zn = zc + sum;
+        bf16x4 p0, p1, p2;
+        split_three4(zn, p0, p1, p2);
+        if (ft < f / 16) {
+          const int n = (c + 1 - blk0) % 3;
+          *reinterpret_cast<f32x4*>(&sh.z[n][r]) = zn;
+          *reinterpret_cast<bf16x4*>(&sh.zp[n][0][r]) = p0;
+          *reinterpret_cast<bf16x4*>(&sh.zp[n][1][r]) = p1;
+          *reinterpret_cast<bf16x4*>(&sh.zp[n][2][r]) = p2;
+          if (last && c + 1 == blk1) *reinterpret_cast<f32x4*>(a.z + ((size_t)slot * Hq + h) * f + r) = zn;
+        }
+      };
       // lin_den = phi(q) . z of block c and the two merge coefficients of
       // each row, for the state waves' merge of block c an iteration later:
       // out = (ca P V + cz phi(Q) S / lin_den) / (ca den + cz), with the
@@ -647,39 +768,39 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
       // the in-block softmax alone.
       auto coefs = [&](int c) {
         const typename C::Buf& Bc = sh.buf[(c - blk0) & 1];
-        const float* zc = sh.z[(c - blk0) % 3];
-        float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        // rows 0, 1, 2 of the left operand: the parts of z (the other rows
+        // repeat the last and are not read); columns: the queries
+        const T* zr = sh.zp[(c - blk0) % 3][min(li, 2)];
+        f32x16 ld = {};
 #pragma unroll
-        for (int r = 0; r < f / 2; r += 8) {
-          const int r0 = hh * (f / 2) + r;
-          const bf16x4 xa = *reinterpret_cast<const bf16x4*>(&Bc.phiQ[li][r0]);
-          const bf16x4 xb = *reinterpret_cast<const bf16x4*>(&Bc.phiQ[li][r0 + 4]);
-          const f32x4 z0v = *reinterpret_cast<const f32x4*>(zc + r0);
-          const f32x4 z1v = *reinterpret_cast<const f32x4*>(zc + r0 + 4);
-          const T xt[8] = {xa[0], xa[1], xa[2], xa[3], xb[0], xb[1], xb[2], xb[3]};
+        for (int k0 = 0; k0 < C::KF; k0 += 4) {
+          op_t za[4], qa[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            part[e] += to_f32(xt[e]) * z0v[e];
-            part[e] += to_f32(xt[4 + e]) * z1v[e];
+          for (int j = 0; j < 4; ++j) {
+            za[j] = lds_op_perm<T>(zr, k0 + j, hh, 0);
+            qa[j] = lds_op_perm<T>(&Bc.phiQ[li][0], k0 + j, hh, 0);
           }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) ld = M::mma(za[j], qa[j], ld);
         }
-        float lden = (part[0] + part[1]) + (part[2] + part[3]);
-        lden += xor32(lden);
+        const float lden = ld[0] + (ld[1] + ld[2]);  // (lanes of the lower half)
         const float m = Bc.m[li], den = Bc.den[li];
         float ca = 1.0f, cz = 0.0f, rz = 0.0f;
         if (lden > 0.0f) {
-          const float la = lw + m, lb = logf(lden);
+          const float la = (lw + m) * kLog2e, lb = __builtin_amdgcn_logf(lden);
           const float cc = fmaxf(la, lb);
-          ca = expf(la - cc);
-          cz = expf(lb - cc);
-          rz = 1.0f / lden;
+          ca = __builtin_amdgcn_exp2f(la - cc);
+          cz = __builtin_amdgcn_exp2f(lb - cc);
+          rz = fast_rcp(lden);
         }
-        const float inv = 1.0f / (ca * den + cz);
+        const float inv = fast_rcp(ca * den + cz);
         if (hh == 0) sh.coef[(c - blk0) & 1][li] = make_float2(ca * inv, cz * rz * inv);
       };
       for (int c = blk0 + par; c < blk1; c += 2) {
         // ---- iteration c-1 ----
         if constexpr (K) {
+          if (c - 4 >= blk0) store_rows(c - 4);
           if (c - 2 >= blk0) coefs(c - 2);
         }
         float phi[C::NPAIR][16];
@@ -689,7 +810,7 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
           // scores: keys in rows, queries in columns
 #pragma unroll
           for (int ks = 0; ks < C::KD; ++ks)
-            sc = M::mma(keep_if<T>(row_ok, xk[ks]), keep_if<T>(row_ok, x[ks]), sc);
+            sc = M::mma(xk[ks], x[ks], sc);  // (rows past L repeat row L-1: masked below, or not stored)
         }
         // (the operands are read by the products above before the rows of
         // this wave's next block land in the same registers)
@@ -715,6 +836,9 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
         }
         lds_barrier();
         // ---- iteration c ----
+        if constexpr (!K) {
+          if (c - 1 >= blk0) z_update(c - 1);
+        }
         fm_second(phi, NA, mnl, sp, sn);
         typename C::Buf& B = sh.buf[(c - blk0) & 1];
         if constexpr (!K) {
@@ -726,11 +850,7 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
 #pragma unroll
           for (int i = 0; i < 16; i += 4) {
             bf16x4 hi4, lo4;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              hi4[e] = (T)pr[i + e];
-              lo4[e] = (T)(pr[i + e] - (float)hi4[e]);
-            }
+            split_hi_lo4(&pr[i], hi4, lo4);
             *reinterpret_cast<bf16x4*>(&B.ph[li][row_of(i, hh)]) = hi4;
             *reinterpret_cast<bf16x4*>(&B.pl[li][row_of(i, hh)]) = lo4;
           }
@@ -739,61 +859,42 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
             B.den[li] = den;
           }
         } else {
+          char* kt = reinterpret_cast<char*>(B.phiK[0]);
+          // (opaque: the piece addresses are formed here, not kept in registers
+          // across the loop, where they would spill)
+          int wb = Tok::write_base(li, hh);
+          asm volatile("" : "+v"(wb));
 #pragma unroll
           for (int p = 0; p < C::NPAIR; ++p)
 #pragma unroll
-            for (int i = 0; i < 16; i += 2)
-              pack_hi_lo2(phi[p][i], phi[p][i + 1], B.phiKT[WFM::feature(16 * p + i, hh)][li],
-                          B.phiKT[WFM::feature(16 * p + i + 1, hh)][li]);
-          // z_{c+1} = z_c + phi(K_c)^T 1: the tile just stored read back in
-          // operand order (this wave's own LDS writes complete first) as
-          // accumulator tiles whose columns are all equal
-          asm volatile("" ::: "memory");
-          PairRaw kz[C::NRT][C::KL];
-#pragma unroll
-          for (int p = 0; p < C::NRT; ++p)
-#pragma unroll
-            for (int ks = 0; ks < C::KL; ++ks) kz[p][ks] = lds_pair_raw(&B.phiKT[p * kTile + li][0], ks, hh);
-          const float* zc = sh.z[(c - blk0) % 3];
-          float* zn = sh.z[(c + 1 - blk0) % 3];
-#pragma unroll
-          for (int p = 0; p < C::NRT; ++p) {
-            f32x16 dz;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) dz[i] = zc[p * kTile + row_of(i, hh)];
-#pragma unroll
-            for (int ks = 0; ks < C::KL; ++ks) {
-              op_t khi, klo;
-              pair_split(kz[p][ks], khi, klo);
-              dz = M::mma(khi, ones, dz);
-              dz = M::mma(klo, ones, dz);
+            for (int i = 0; i < 16; i += 4) {  // features 32p + 2i + 4hh ..
+              bf16x4 hi4, lo4;
+              split_hi_lo4(&phi[p][i], hi4, lo4);
+              const int at = wb ^ (16 * (4 * p + i / 4));
+              *reinterpret_cast<bf16x4*>(kt + at) = hi4;
+              *reinterpret_cast<bf16x4*>(kt + at + Tok::kPlane * 2) = lo4;
             }
-            if (li == 0) {
-#pragma unroll
-              for (int i = 0; i < 16; i += 4)
-                *reinterpret_cast<f32x4*>(&zn[p * kTile + row_of(i, hh)]) =
-                    f32x4{dz[i], dz[i + 1], dz[i + 2], dz[i + 3]};
-              if (last && c + 1 == blk1) {
-                float* zh = a.z + ((size_t)slot * Hq + h) * f;
-#pragma unroll
-                for (int i = 0; i < 16; i += 4)
-                  *reinterpret_cast<f32x4*>(zh + p * kTile + row_of(i, hh)) =
-                      f32x4{dz[i], dz[i + 1], dz[i + 2], dz[i + 3]};
-              }
-            }
-          }
         }
         lds_barrier();
         nbar += 2;
       }
-      // the coefficients of this wave's last block, an iteration after it
-      if constexpr (K) {
-        const int clast = blk0 + par + 2 * ((blk1 - blk0 - par - 1) / 2);
-        if (clast >= blk0 + par && clast < blk1) {
-          coefs(clast);
-          lds_barrier();
-          ++nbar;
+      // what is left of the earlier blocks, each in its iteration: the output
+      // stores and the last coefficients (K), the last z (QS)
+      int c = blk0 + par;
+      if (c < blk1) c += (blk1 - c + 1) / 2 * 2;
+      for (; c - 1 <= blk1 + 2; c += 2) {
+        if constexpr (K) {
+          if (c - 4 >= blk0 && c - 4 < blk1) store_rows(c - 4);
+          if (c - 2 >= blk0 && c - 2 < blk1) coefs(c - 2);
         }
+        lds_barrier();
+        ++nbar;
+        if (c > blk1 + 2) break;
+        if constexpr (!K) {
+          if (c - 1 >= blk0 && c - 1 < blk1) z_update(c - 1);
+        }
+        lds_barrier();
+        ++nbar;
       }
       for (; nbar < nit; ++nbar) lds_barrier();
     };
@@ -821,50 +922,36 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
       }
     // V rows of this wave's 32 columns, one block ahead: 4 lanes per row
     // (16 bytes each), 16 rows per load; a row at or past the block length
-    // reads the next rows of the request (zero past its end) and is zeroed
-    // when the operands are formed.  The V^T operands (lane li: column
-    // 32cw + li; k-step ks: the tokens row_of(ks*E + e, hh), the order in
-    // which P and phi(K)^T enter the products) are then read from this
-    // wave's LDS copy of the rows.
-    const int vlane = ((lane >> 2) * (int)kstride + cw * kTile + (lane & 3) * 8) * (int)sizeof(T);
+    // reads past the buffer's end, as zeros.  The V^T operands (lane li:
+    // column 32cw + li; k-step ks: the tokens row_of(ks*E + e, hh), the order
+    // in which P and phi(K)^T enter the products) are then read, transposed,
+    // from this wave's LDS copy of the rows (four rows are all of the banks).
+    int vlane[2];
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+      const int t = s2 * 16 + (lane >> 2);
+      vlane[s2] = t < L ? (t * (int)kstride + cw * kTile + (lane & 3) * 8) * (int)sizeof(T) : kPastBuffer;
+    }
     op_t vrow[2];
     auto load_v = [&](int blk) {
       const int so = koff(blk);
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2)
-        vrow[s2] = buf_op<T>(vrs, vlane, so + s2 * 16 * (int)(kstride * sizeof(T)));
+      for (int s2 = 0; s2 < 2; ++s2) vrow[s2] = buf_op<T>(vrs, vlane[s2], so);
     };
-    T (*vt)[kTile + 8] = sh.vt[cw];
+    T (*vt)[kTile] = sh.vt[cw];
+    const int krb0 = Tok::read_base(lane);
+    const T* vtr = &vt[4 * hh + ((lane & 15) >> 2)][16 * ((lane >> 4) & 1) + 4 * (lane & 3)];
     if (blk0 < blk1) load_v(blk0);
     // the products of a block, kept from its iteration to its merge in the
     // next
     f32x16 olin = {}, apv = {};
     constexpr int RH = (C::NRT + 1) / 2;
-    for (int it = blk0 - 1; it <= blk1 + 2; ++it) {
-      const int cr = it - 1, cm = it - 2, cs = it - 3;
-      // ---- output store of block cs: this wave's share of the rows of the
-      // staging tile, D/8 lanes per row (8 columns, 16 bytes of bf16, each),
-      // so that every store covers whole rows ----
-      if (cs >= blk0 && cs < blk1) {
-        const float (*st)[D + 4] = sh.stage[(cs - blk0) & 1];
-        constexpr int LPR = D / 8, RPW = kTile / NC;  // lanes per row, rows per wave
-#pragma unroll
-        for (int pass = 0; pass < RPW * LPR / kWave; ++pass) {
-          const int t = cw * RPW + pass * (kWave / LPR) + lane / LPR, c8 = (lane % LPR) * 8;
-          if (t < L) {
-            const f32x4 x0 = *reinterpret_cast<const f32x4*>(&st[t][c8]);
-            const f32x4 x1 = *reinterpret_cast<const f32x4*>(&st[t][c8 + 4]);
-            const float o8[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
-            const size_t oidx = (((size_t)b * T_ + (size_t)cs * L + t) * Hq + h) * D + c8;
-            store_out8<T>(a.out, oidx, o8, a.s.out_f32);
-          }
-        }
-      }
-      // ---- merge of block cm into the staging tile (this wave's columns);
-      // stored by all state waves after the next barrier ----
-      if (cm >= blk0 && cm < blk1 && row_ok) {
-        const float2 cf = sh.coef[(cm - blk0) & 1][li];
-        float (*st)[D + 4] = sh.stage[(cm - blk0) & 1];
+    // The merge of block cm into the staging tile (this wave's columns),
+    // which the K waves store after the next barrier.
+    const bool out_f32 = a.s.out_f32;
+    auto merge = [&](int cm, const float2& cf) __attribute__((always_inline)) {
+      float (*st)[D + 4] = sh.stage[(cm - blk0) & 1];
+      if (out_f32) {
 #pragma unroll
         for (int i = 0; i < 16; i += 4) {
           f32x4 o;
@@ -872,33 +959,48 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
           for (int e = 0; e < 4; ++e) o[e] = cf.x * apv[i + e] + cf.y * olin[i + e];
           *reinterpret_cast<f32x4*>(&st[li][cw * kTile + row_of(i, hh)]) = o;
         }
-      }
-      if (cr >= blk0 && cr < blk1) {
-        typename C::Buf& B = sh.buf[(cr - blk0) & 1];
-        // LDS operands are requested in batches ahead of the products that
-        // use them, a scheduling barrier after each batch: fetched one at a
-        // time next to its product, every operand costs a full LDS round
-        // trip.  Batch 1: the operands of the readout.
-        op_t pb[C::KF];
+      } else {
+        char* sb = reinterpret_cast<char*>(st);
 #pragma unroll
-        for (int ks = 0; ks < C::KF; ++ks) pb[ks] = lds_op_perm<T>(&B.phiQ[li][0], ks, hh, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        // V^T operands of block cr through this wave's LDS rows (its own
-        // writes complete before its reads), the next block's rows issued
+        for (int i = 0; i < 16; i += 4) {
+          bf16x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = (T)(cf.x * apv[i + e] + cf.y * olin[i + e]);
+          *reinterpret_cast<bf16x4*>(sb + StageRow<D>::at(li, cw * kTile + row_of(i, hh))) = o;
+        }
+      }
+    };
+    lds_barrier();  // iterations blk0-1 and blk0: nothing to do yet
+    lds_barrier();
+    for (int cr = blk0; cr < blk1; ++cr) {  // iteration cr + 1
+      const int cm = cr - 1;
+      {
+        typename C::Buf& B = sh.buf[(cr - blk0) & 1];
+        int krb = krb0;  // (opaque: the operand addresses are formed per block)
+        asm volatile("" : "+v"(krb));
+        // V rows of block cr through this wave's LDS tile (its own writes
+        // complete before its reads), the next block's rows issued
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2)
           *reinterpret_cast<op_t*>(&vt[s2 * 16 + (lane >> 2)][(lane & 3) * 8]) = vrow[s2];
         __builtin_amdgcn_sched_barrier(0);
         if (cr + 1 < blk1) load_v(cr + 1);
+        // LDS operands are requested in batches ahead of the products that
+        // use them, a scheduling barrier after each batch: fetched one at a
+        // time next to its product, every operand costs a full LDS round
+        // trip.  Batch 1: the coefficients of the block before, the
+        // operands of the readout and V^T.
+        const float2 cf = sh.coef[(cm - blk0) & 1][li];
         asm volatile("" ::: "memory");
+        op_t pb[C::KF];
+#pragma unroll
+        for (int ks = 0; ks < C::KF; ++ks) pb[ks] = lds_op_perm<T>(&B.phiQ[li][0], ks, hh, 0);
         op_t vk[C::KL];
 #pragma unroll
         for (int ks = 0; ks < C::KL; ++ks)
-#pragma unroll
-          for (int e = 0; e < E; ++e) {
-            const int t = row_of(ks * E + e, hh);
-            vk[ks][e] = t < L ? vt[t][li] : (T)0.0f;
-          }
+          vk[ks] = lds_tr_op(vtr + 16 * ks * kTile, vtr + (16 * ks + 8) * kTile);
+        __builtin_amdgcn_sched_barrier(0);
+        if (cm >= blk0) merge(cm, cf);
         __builtin_amdgcn_sched_barrier(0);
         // readout against the state of the blocks before cr
         f32x16 ol = {};
@@ -916,7 +1018,7 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
         // Batch 2: P of block cr and the commit operands of the first half
         // of the row tiles.
         op_t pph[C::KL], ppl[C::KL];
-        PairRaw kr[RH][C::KL];
+        op_t kh[RH][C::KL], kl[RH][C::KL];
 #pragma unroll
         for (int ks = 0; ks < C::KL; ++ks) {
           pph[ks] = lds_op_perm<T>(&B.ph[li][0], ks, hh, 0);
@@ -925,7 +1027,10 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
 #pragma unroll
         for (int rt = 0; rt < RH; ++rt)
 #pragma unroll
-          for (int ks = 0; ks < C::KL; ++ks) kr[rt][ks] = lds_pair_raw(&B.phiKT[rt * kTile + li][0], ks, hh);
+          for (int ks = 0; ks < C::KL; ++ks) {
+            kh[rt][ks] = Tok::op(B.phiK[0], krb, rt, ks);
+            kl[rt][ks] = Tok::op(B.phiK[1], krb, rt, ks);
+          }
         __builtin_amdgcn_sched_barrier(0);
         // P V of this wave's columns (P as a bf16 pair hi + lo)
         f32x16 pv = {};
@@ -939,35 +1044,37 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
         for (int rt = 0; rt < RH; ++rt)
 #pragma unroll
           for (int ks = 0; ks < C::KL; ++ks) {
-            op_t khi, klo;
-            pair_split(kr[rt][ks], khi, klo);
-            sacc[rt] = M::mma(khi, vk[ks], sacc[rt]);
-            sacc[rt] = M::mma(klo, vk[ks], sacc[rt]);
+            sacc[rt] = M::mma(kh[rt][ks], vk[ks], sacc[rt]);
+            sacc[rt] = M::mma(kl[rt][ks], vk[ks], sacc[rt]);
           }
         __builtin_amdgcn_sched_barrier(0);
         // Batch 3: the commit operands of the other row tiles.
-        PairRaw kr2[C::NRT - RH][C::KL];
+        op_t kh2[C::NRT - RH][C::KL], kl2[C::NRT - RH][C::KL];
 #pragma unroll
         for (int rt = RH; rt < C::NRT; ++rt)
 #pragma unroll
-          for (int ks = 0; ks < C::KL; ++ks)
-            kr2[rt - RH][ks] = lds_pair_raw(&B.phiKT[rt * kTile + li][0], ks, hh);
+          for (int ks = 0; ks < C::KL; ++ks) {
+            kh2[rt - RH][ks] = Tok::op(B.phiK[0], krb, rt, ks);
+            kl2[rt - RH][ks] = Tok::op(B.phiK[1], krb, rt, ks);
+          }
         __builtin_amdgcn_sched_barrier(0);
         // commit, second half
 #pragma unroll
         for (int rt = RH; rt < C::NRT; ++rt)
 #pragma unroll
           for (int ks = 0; ks < C::KL; ++ks) {
-            op_t khi, klo;
-            pair_split(kr2[rt - RH][ks], khi, klo);
-            sacc[rt] = M::mma(khi, vk[ks], sacc[rt]);
-            sacc[rt] = M::mma(klo, vk[ks], sacc[rt]);
+            sacc[rt] = M::mma(kh2[rt - RH][ks], vk[ks], sacc[rt]);
+            sacc[rt] = M::mma(kl2[rt - RH][ks], vk[ks], sacc[rt]);
           }
         olin = ol;
         apv = pv;
       }
       lds_barrier();
     }
+    // iterations blk1+1 and blk1+2: the last block's merge (and its store)
+    merge(blk1 - 1, sh.coef[(blk1 - 1 - blk0) & 1][li]);
+    lds_barrier();
+    lds_barrier();
     if (last) {
 #pragma unroll
       for (int rt = 0; rt < C::NRT; ++rt)
@@ -986,14 +1093,19 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
 // blocks per iteration, 4 + D/32 waves:
 //   feature-map waves (4): phi(K) of the piece's blocks, wave w taking the
 //     blocks 4m + w; a map spans two iterations (the logits, the row extremes
-//     and most exponentials, then the rest and the store of phi(K)^T as
-//     hi | lo pairs), so the four waves finish a pair per iteration;
+//     and most exponentials, then the rest and the store of phi(K) as rows of
+//     hi and lo planes, TokTile), so the four waves finish a pair per
+//     iteration;
 //   state waves (D/32): the commit of the previous pair into S columns
 //     32w .. 32w+31 and dz (as phi(K)^T 1) in fp32 accumulators, with the V^T
 //     operands of their columns from whole V rows through a per-wave LDS
 //     tile.
-// One barrier per iteration; phi(K)^T is double-buffered (written in
-// iteration j for pair j, read in j + 1).
+// One barrier per iteration; phi(K) is double-buffered (written in iteration
+// j for pair j, read in j + 1).  Bound by the state waves' LDS reads (44 KB a
+// wave and pair) between their products; 8 x 8192 tokens without outputs: 138 us
+// with phi(K)^T as hi | lo pairs in dwords and V^T by an identity product,
+// 115 us with transposing reads.  Requesting each batch of operands a batch
+// ahead of its products was slower (122 us).
 // ---------------------------------------------------------------------------
 template <typename T, int D, int F>
 struct DeltaPipeCfg {
@@ -1010,11 +1122,11 @@ struct DeltaPipeCfg {
   static constexpr int KL = kTile / M::KW;
   typedef WaveFeatMap<T, D, F> WFM;
   struct alignas(16) Buf {
-    uint32_t phiKT[2][f][kTile + 4];     // per block of the pair: bf16 hi | lo << 16
+    T phiK[2][2][kTile * f];             // per block of the pair: planes hi and lo (TokTile)
   };
   struct alignas(16) Smem {
     Buf buf[2];
-    T vt[NC][2][kTile][kTile + 8];       // V rows of each state wave's columns
+    T vt[NC][2][kTile][kTile];           // V rows of each state wave's columns
   };
 };
 
@@ -1030,6 +1142,7 @@ __global__ __launch_bounds__(delta_pipe_threads<D>()) void hyb_prefill_delta_pip
   typedef typename C::M M;
   typedef typename C::op_t op_t;
   typedef typename C::WFM WFM;
+  typedef TokTile<2 * F> Tok;
   constexpr int f = C::f, E = M::E, KW = M::KW, NT = C::NT, NC = C::NC;
   static_assert(sizeof(T) == 2, "the pipelined increment is the bf16 path");
   static_assert(delta_pipe_threads<D>() == kWave * C::NWAVE, "launch bounds match the waves");
@@ -1156,13 +1269,21 @@ __global__ __launch_bounds__(delta_pipe_threads<D>()) void hyb_prefill_delta_pip
           phi[NT + t][i] *= in;
         }
       const int j = (c - blk0) >> 1;
-      uint32_t (*kt)[kTile + 4] = sh.buf[j & 1].phiKT[w & 1];
+      char* kt = reinterpret_cast<char*>(sh.buf[j & 1].phiK[w & 1][0]);
+      // (opaque: the piece addresses are formed here, not kept in registers
+      // across the loop)
+      int wb = Tok::write_base(li, hh);
+      asm volatile("" : "+v"(wb));
 #pragma unroll
       for (int p = 0; p < C::NPAIR; ++p)
 #pragma unroll
-        for (int i = 0; i < 16; i += 2)
-          pack_hi_lo2(phi[p][i], phi[p][i + 1], kt[WFM::feature(16 * p + i, hh)][li],
-                      kt[WFM::feature(16 * p + i + 1, hh)][li]);
+        for (int i = 0; i < 16; i += 4) {  // features 32p + 2i + 4hh ..
+          bf16x4 hi4, lo4;
+          split_hi_lo4(&phi[p][i], hi4, lo4);
+          const int at = wb ^ (16 * (4 * p + i / 4));
+          *reinterpret_cast<bf16x4*>(kt + at) = hi4;
+          *reinterpret_cast<bf16x4*>(kt + at + Tok::kPlane * 2) = lo4;
+        }
       lds_barrier();
       nbar += 2;
     }
@@ -1180,26 +1301,25 @@ __global__ __launch_bounds__(delta_pipe_threads<D>()) void hyb_prefill_delta_pip
     for (int j = 0; j < C::ZPW; ++j) zt[j] = f32x16{};
     // V rows of this wave's 32 columns for both blocks of a pair, an
     // iteration ahead: 4 lanes per row (16 bytes each), 16 rows per load; a
-    // row at or past the block length reads the next rows of the request
-    // (zero past its end) and is zeroed when the operands are formed
-    const int vlane = ((lane >> 2) * (int)kstride + cw * kTile + (lane & 3) * 8) * (int)sizeof(T);
+    // row at or past the block length reads past the buffer's end, as zeros
+    int vlane[2];
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+      const int t = s2 * 16 + (lane >> 2);
+      vlane[s2] = t < L ? (t * (int)kstride + cw * kTile + (lane & 3) * 8) * (int)sizeof(T) : kPastBuffer;
+    }
     op_t vrow[2][2];
     auto load_v = [&](int j) {
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        const int blk = min(blk0 + 2 * j + q, blk1 - 1);
-        const int so = koff(blk);
+        const int so = koff(min(blk0 + 2 * j + q, blk1 - 1));
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2)
-          vrow[q][s2] = buf_op<T>(vrs, vlane, so + s2 * 16 * (int)(kstride * sizeof(T)));
+        for (int s2 = 0; s2 < 2; ++s2) vrow[q][s2] = buf_op<T>(vrs, vlane[s2], so);
       }
     };
+    const int krb0 = Tok::read_base(lane);
+    const T* vtr = &sh.vt[cw][0][4 * hh + ((lane & 15) >> 2)][16 * ((lane >> 4) & 1) + 4 * (lane & 3)];
     if (npair > 0) load_v(0);
-    op_t ident[C::KL];
-#pragma unroll
-    for (int ks = 0; ks < C::KL; ++ks)
-#pragma unroll
-      for (int e = 0; e < E; ++e) ident[ks][e] = (T)(ks * KW + hh * E + e == li ? 1.0f : 0.0f);
     constexpr int RH = (C::NRT + 1) / 2;
     for (int i = -1; i <= npair; ++i) {
       const int j = i - 1;
@@ -1215,68 +1335,64 @@ __global__ __launch_bounds__(delta_pipe_threads<D>()) void hyb_prefill_delta_pip
         __builtin_amdgcn_sched_barrier(0);
         if (j + 1 < npair) load_v(j + 1);
         asm volatile("" ::: "memory");
-        // read back as operands (lane li: token li, 16 contiguous bytes of
-        // columns per k-step; padding tokens zeroed) and transposed on the
-        // MFMAs as V^T = (V I)^T, exact: one nonzero product per entry
-        op_t vr[2][C::KL];
+        // read back transposed (lane li: column 32cw + li at the tokens
+        // row_of(ks*E + e, hh))
+        op_t vk[2][C::KL];
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
-          for (int ks = 0; ks < C::KL; ++ks) vr[q][ks] = load_op<T>(&sh.vt[cw][q][li][ks * KW + hh * E]);
+          for (int ks = 0; ks < C::KL; ++ks)
+            vk[q][ks] = lds_tr_op(vtr + (q * kTile + 16 * ks) * kTile, vtr + (q * kTile + 16 * ks + 8) * kTile);
         __builtin_amdgcn_sched_barrier(0);
-        op_t vk[2][C::KL];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          f32x16 va = {};
-#pragma unroll
-          for (int ks = 0; ks < C::KL; ++ks) va = M::mma(keep_if<T>(row_ok, vr[q][ks]), ident[ks], va);
-#pragma unroll
-          for (int ks = 0; ks < C::KL; ++ks) vk[q][ks] = acc_op_exact<T>(va, ks);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        int krb = krb0;  // (opaque: the operand addresses are formed per pair)
+        asm volatile("" : "+v"(krb));
         // LDS operands in batches ahead of their products (a scheduling
         // barrier after each batch): per block of the pair, the first half
         // of the row tiles, then the rest with z
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
           if (blk0 + 2 * j + q >= blk1) continue;  // uniform
-          PairRaw kr[RH][C::KL];
+          op_t kh[RH][C::KL], kl[RH][C::KL];
 #pragma unroll
           for (int rt = 0; rt < RH; ++rt)
 #pragma unroll
-            for (int ks = 0; ks < C::KL; ++ks) kr[rt][ks] = lds_pair_raw(&B.phiKT[q][rt * kTile + li][0], ks, hh);
+            for (int ks = 0; ks < C::KL; ++ks) {
+              kh[rt][ks] = Tok::op(B.phiK[q][0], krb, rt, ks);
+              kl[rt][ks] = Tok::op(B.phiK[q][1], krb, rt, ks);
+            }
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int rt = 0; rt < RH; ++rt)
 #pragma unroll
             for (int ks = 0; ks < C::KL; ++ks) {
-              op_t khi, klo;
-              pair_split(kr[rt][ks], khi, klo);
-              sacc[rt] = M::mma(khi, vk[q][ks], sacc[rt]);
-              sacc[rt] = M::mma(klo, vk[q][ks], sacc[rt]);
+              sacc[rt] = M::mma(kh[rt][ks], vk[q][ks], sacc[rt]);
+              sacc[rt] = M::mma(kl[rt][ks], vk[q][ks], sacc[rt]);
             }
           __builtin_amdgcn_sched_barrier(0);
-          PairRaw kr2[C::NRT - RH][C::KL], zr2[C::ZPW][C::KL];
+          op_t kh2[C::NRT - RH][C::KL], kl2[C::NRT - RH][C::KL], zh[C::ZPW][C::KL], zl[C::ZPW][C::KL];
 #pragma unroll
           for (int rt = RH; rt < C::NRT; ++rt)
 #pragma unroll
-            for (int ks = 0; ks < C::KL; ++ks)
-              kr2[rt - RH][ks] = lds_pair_raw(&B.phiKT[q][rt * kTile + li][0], ks, hh);
+            for (int ks = 0; ks < C::KL; ++ks) {
+              kh2[rt - RH][ks] = Tok::op(B.phiK[q][0], krb, rt, ks);
+              kl2[rt - RH][ks] = Tok::op(B.phiK[q][1], krb, rt, ks);
+            }
 #pragma unroll
           for (int jz = 0; jz < C::ZPW; ++jz) {
             const int p = min(cw + jz * NC, C::NRT - 1);
 #pragma unroll
-            for (int ks = 0; ks < C::KL; ++ks) zr2[jz][ks] = lds_pair_raw(&B.phiKT[q][p * kTile + li][0], ks, hh);
+            for (int ks = 0; ks < C::KL; ++ks) {
+              zh[jz][ks] = Tok::op(B.phiK[q][0], krb, p, ks);
+              zl[jz][ks] = Tok::op(B.phiK[q][1], krb, p, ks);
+            }
           }
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int rt = RH; rt < C::NRT; ++rt)
 #pragma unroll
             for (int ks = 0; ks < C::KL; ++ks) {
-              op_t khi, klo;
-              pair_split(kr2[rt - RH][ks], khi, klo);
-              sacc[rt] = M::mma(khi, vk[q][ks], sacc[rt]);
-              sacc[rt] = M::mma(klo, vk[q][ks], sacc[rt]);
+              sacc[rt] = M::mma(kh2[rt - RH][ks], vk[q][ks], sacc[rt]);
+              sacc[rt] = M::mma(kl2[rt - RH][ks], vk[q][ks], sacc[rt]);
             }
 #pragma unroll
           for (int jz = 0; jz < C::ZPW; ++jz) {
@@ -1284,10 +1400,8 @@ __global__ __launch_bounds__(delta_pipe_threads<D>()) void hyb_prefill_delta_pip
             if (p >= C::NRT) continue;  // uniform
 #pragma unroll
             for (int ks = 0; ks < C::KL; ++ks) {
-              op_t khi, klo;
-              pair_split(zr2[jz][ks], khi, klo);
-              zt[jz] = M::mma(khi, ones, zt[jz]);
-              zt[jz] = M::mma(klo, ones, zt[jz]);
+              zt[jz] = M::mma(zh[jz][ks], ones, zt[jz]);
+              zt[jz] = M::mma(zl[jz][ks], ones, zt[jz]);
             }
           }
         }

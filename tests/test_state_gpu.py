@@ -258,3 +258,32 @@ def test_prefill_plans(shape):
         rest = np.setdiff1d(np.arange(B + 1), at[:n])
         assert np.array_equal(Sh[rest], S0[rest].astype(np.float64))
         assert np.array_equal(zh[rest], z0[rest].astype(np.float64))
+
+
+@pytest.mark.parametrize("L,d,F", [(5, 128, 64), (31, 64, 32), (17, 128, 32), (32, 64, 64)])
+def test_prefill_blocks_stay_apart(L, d, F):
+    """The walk loads whole 32-row tiles: what follows a block's rows (here a
+    last block full of NaN) plays no part in its outputs, and the blocks
+    before it answer as they do without it, bit for bit."""
+    nblk, Hq, Hkv = 9, 4, 2
+    dims = synth.Dims(B=2, Hq=Hq, Hkv=Hkv, d=d, L=L, F=F, dtype="bf16")
+    announce(f"prefill blocks apart L={L} d={d} F={F}")
+    q, k, v = synth.block_qkv(dims.with_(L=nblk * L), 211, 1.0)
+    Wt, alpha = synth.feature_weights(dims, 212, 213, 1.0 / np.sqrt(d))
+    W, al = act(Wt, "bf16"), f32(alpha)
+    outs = []
+    for bad in (False, True):
+        x = [act(t, "bf16") for t in (q, k, v)]
+        if bad:
+            for t in x:
+                t[:, -L:] = float("nan")
+        S = torch.zeros((2, Hq, d, 2 * F), device="cuda")
+        z = torch.zeros((2, Hq, 2 * F), device="cuda")
+        for out_f32 in (False, True):
+            outs.append(hb.hybrid_state_prefill(*x, W, al, S.clone(), z.clone(), L, out_f32=out_f32))
+    torch.cuda.synchronize()
+    n = (nblk - 1) * L
+    for clean, dirty in ((outs[0], outs[2]), (outs[1], outs[3])):
+        assert torch.isfinite(dirty[:, :n]).all()
+        assert torch.equal(clean[:, :n], dirty[:, :n])
+        assert torch.isnan(dirty[:, n:]).all()
