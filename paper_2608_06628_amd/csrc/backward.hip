@@ -1864,7 +1864,7 @@ constexpr int rwalk_threads() {
   return kWave * (4 + D / kTile);
 }
 
-template <int D, int F>
+template <int D, int F, bool IN>
 __global__ __launch_bounds__(rwalk_threads<D>()) void hyb_bwd_rwalk_kernel(BwdKArgs ka) {
   typedef RWalkCfg<D, F> C;
   typedef typename C::M M;
@@ -1898,6 +1898,32 @@ __global__ __launch_bounds__(rwalk_threads<D>()) void hyb_bwd_rwalk_kernel(BwdKA
   };
   auto vrowp = [&](int blk) {
     return (const bf16*)a.v + (((size_t)b * T_ + (size_t)blk * L) * Hkv + g) * D;
+  };
+
+  // With the input gradients (IN): dL/du of the keys of step n (1 .. nb), both
+  // signs summed (each as its pair hi + lo), for dL/dk = W_h dL/du.  The
+  // producers write it, a quarter each, after the step's second barrier: the
+  // state waves post the next dL/du after the next first barrier.
+  auto write_duk = [&](int n) {
+    if constexpr (!IN) return;
+    if (n < 1) return;
+    float* dst = ka.duk + ((size_t)u * T_ + (size_t)blk_of(n - 1) * L) * F;
+    for (int it = tid; it < L * (F / 4); it += NP * kWave) {
+      const int t = it / (F / 4), j4 = (it % (F / 4)) * 4;
+      f32x4 x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int sg = 0; sg < 2; ++sg) {
+          const uint32_t pk = sh.duT[sg][j4 + e][t];
+          acc += unpack_hi(pk);
+          acc += unpack_lo(pk);
+        }
+        x[e] = acc;
+      }
+      *reinterpret_cast<f32x4*>(dst + (size_t)t * F + j4) = x;
+    }
   };
 
   lds_barrier();
@@ -1938,9 +1964,11 @@ __global__ __launch_bounds__(rwalk_threads<D>()) void hyb_bwd_rwalk_kernel(BwdKA
                   f32x4{phi[p][i], phi[p][i + 1], phi[p][i + 2], phi[p][i + 3]};
         }
       }
+      write_duk(n - 1);
       lds_barrier();
       lds_barrier();
     }
+    write_duk(nb);
   } else if (w == 2) {
     // ---- V rows (operands of dL/dphi(K)) and K^T (operands of dW) ----
     op_t vr[NC][C::KL], kt[NC][C::KL];
@@ -1967,9 +1995,11 @@ __global__ __launch_bounds__(rwalk_threads<D>()) void hyb_bwd_rwalk_kernel(BwdKA
           }
         if (n + 1 < nb) load(blk_of(n + 1));
       }
+      write_duk(n - 1);
       lds_barrier();
       lds_barrier();
     }
+    write_duk(nb);
   } else if (w == 3) {
     // ---- dL/dN^T hi/lo operands (tokens natural) and dL/dD ----
     f32x4 graw[NC][C::KL][2];
@@ -2002,9 +2032,11 @@ __global__ __launch_bounds__(rwalk_threads<D>()) void hyb_bwd_rwalk_kernel(BwdKA
         if (lane < kTile) B.gd[lane] = gdv;
         if (n + 1 < nb) load(blk_of(n + 1));
       }
+      write_duk(n - 1);
       lds_barrier();
       lds_barrier();
     }
+    write_duk(nb);
   } else {
     // ---- state waves ----
     const int cw = w - NP, col = cw * kTile + li;
@@ -2161,6 +2193,242 @@ __global__ __launch_bounds__(rwalk_threads<D>()) void hyb_bwd_rwalk_kernel(BwdKA
     for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int i = 0; i < 16; ++i) dwk[(size_t)(t * kTile + row_of(i, hh)) * D + col] = dwacc[t][i];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// 5. The state part of dL/dv (bf16): dvl_t = Gbar_c^T phi(k_t), Gbar_c the sum
+// over the queries of the blocks after c of phi(q_i) dL/dN_i^T.  The reverse
+// walk above keeps Gbar split by feature, which this product contracts over,
+// so this walk keeps it split by column: the prefill's walk run backwards,
+// phi(K) reading the state that phi(Q)^T dL/dN is committed to.  One workgroup
+// of 4 + D/32 waves per (request, head, segment), position n being block
+// blk1 - 1 - n:
+//   waves 0, 1: phi(Q) of the even and the odd positions, a map over two
+//     iterations, stored as rows of hi and lo planes (TokTile);
+//   waves 2, 3: phi(K) likewise, as rows in operand order;
+//   state waves: Gbar columns 32w .. 32w+31 of all f rows in fp32
+//     accumulators; per position the readout (rows to dvl) and the commit,
+//     both operands as hi + lo pairs (three products).
+// One barrier per iteration, double-buffered.
+// In one kernel with dL/dphi(K) and the key part of dW (hyb_bwd_rev_kernel)
+// Gbar went through LDS every block: 256 us for 4 x 2048 tokens, where this
+// walk (61 us) and the pipelined reverse walk (88 us) take 149 us together.
+// ---------------------------------------------------------------------------
+template <int D, int F>
+struct DvCfg {
+  typedef Mma<bf16> M;
+  typedef typename M::op_t op_t;
+  static constexpr int NC = D / kTile;
+  static constexpr int NP = 4;
+  static constexpr int NWAVE = NP + NC;
+  static constexpr int f = 2 * F;
+  static constexpr int NRT = f / kTile;
+  static constexpr int KD = D / M::KW;
+  static constexpr int KL = kTile / M::KW;
+  static constexpr int KF = f / M::KW;
+  static constexpr int KLD = f + 4;        // (an odd number of dword pairs)
+  typedef WaveFeatMap<bf16, D, F> WFM;
+  struct alignas(16) Buf {                 // written in iteration n, read in n + 1
+    bf16 phiK[2][kTile][KLD];              // phi(k_t)[r] at [part][t][r]
+    bf16 phiQ[2][kTile * f];               // phi(q_i): planes hi and lo (TokTile)
+  };
+  struct alignas(16) Smem {
+    Buf buf[2];
+  };
+};
+
+template <int D>
+constexpr int dv_threads() {
+  return kWave * (4 + D / kTile);
+}
+
+template <int D, int F>
+__global__ __launch_bounds__(dv_threads<D>()) void hyb_bwd_dv_kernel(BwdKArgs ka) {
+  typedef DvCfg<D, F> C;
+  typedef typename C::M M;
+  typedef typename C::op_t op_t;
+  typedef typename C::WFM WFM;
+  typedef TokTile<2 * F> Tok;
+  constexpr int f = C::f, E = M::E, KW = M::KW, NP = C::NP, NRT = C::NRT, KL = C::KL;
+  static_assert(dv_threads<D>() == kWave * C::NWAVE, "launch bounds match the waves");
+  __shared__ typename C::Smem sh;
+  const BackwardArgs& a = ka.a;
+
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int li = lane & 31, hh = lane >> 5;
+  const int Hq = a.s.Hq, Hkv = a.s.Hkv, L = a.s.L, T_ = a.T;
+  const int units = a.s.B * Hq, nseg = ka.nseg;
+  const int vix = xcd_unit(blockIdx.x, units * nseg);
+  const int u = vix % units, seg = vix / units;
+  const int b = u / Hq, h = u % Hq, g = h / (Hq / Hkv);
+  const int blk0 = seg * ka.seg_blocks, blk1 = min(ka.nblk, blk0 + ka.seg_blocks);
+  const int nb = blk1 - blk0;
+  const int nit = nb + 2;  // iterations -1 .. nb
+  const bool row_ok = li < L;
+  const int lrow = min(li, L - 1);
+  auto blk_of = [&](int n) { return blk1 - 1 - n; };
+
+  if (w < NP) {
+    // ---- feature maps: position n = par + 2j, the map in iteration n - 1,
+    // its store in iteration n; the odd wave idles in the first iteration and
+    // both after their last position, so that every wave passes nit barriers
+    const int par = w & 1;
+    auto role = [&](auto key) {
+      constexpr bool K = decltype(key)::value;
+      const size_t stride = (size_t)(K ? Hkv : Hq) * D;
+      const bf16* base = (const bf16*)(K ? a.k : a.q) + (size_t)b * T_ * stride + (size_t)(K ? g : h) * D +
+                         (size_t)lrow * stride + hh * E;
+      op_t wop[WFM::NT][C::KD], x[C::KD];
+      WFM::load_w((const bf16*)a.W + (size_t)h * F * D, li, hh, wop);
+      auto load = [&](int n) {
+        const bf16* row = base + (size_t)blk_of(n) * L * stride;
+#pragma unroll
+        for (int ks = 0; ks < C::KD; ++ks) x[ks] = load_op<bf16>(row + ks * KW);
+      };
+      if (par < nb) load(par);
+      int nbar = 0;
+      if (par) {
+        lds_barrier();
+        ++nbar;
+      }
+      for (int n = par; n < nb; n += 2) {
+        // (a padding row reads row L-1, finite; row_ok zeroes its phi)
+        float phi[WFM::NPAIR][16];
+        WFM::logits(wop, x, phi);
+        __builtin_amdgcn_sched_barrier(0);
+        if (n + 2 < nb) load(n + 2);
+        WFM::softmax(phi, row_ok);
+        lds_barrier();
+        typename C::Buf& B = sh.buf[n & 1];
+        int wb = Tok::write_base(li, hh);  // (opaque: addresses formed here, not kept)
+        asm volatile("" : "+v"(wb));
+        char* qt = reinterpret_cast<char*>(B.phiQ[0]);
+#pragma unroll
+        for (int p = 0; p < WFM::NPAIR; ++p)
+#pragma unroll
+          for (int i = 0; i < 16; i += 4) {  // features 32p + 2i + 4hh ..
+            bf16x4 hi4, lo4;
+            split_hi_lo4(&phi[p][i], hi4, lo4);
+            if constexpr (K) {
+              *reinterpret_cast<bf16x4*>(&B.phiK[0][li][p * kTile + row_of(i, hh)]) = hi4;
+              *reinterpret_cast<bf16x4*>(&B.phiK[1][li][p * kTile + row_of(i, hh)]) = lo4;
+            } else {
+              const int at = wb ^ (16 * (4 * p + i / 4));
+              *reinterpret_cast<bf16x4*>(qt + at) = hi4;
+              *reinterpret_cast<bf16x4*>(qt + at + Tok::kPlane * 2) = lo4;
+            }
+          }
+        lds_barrier();
+        nbar += 2;
+      }
+      for (; nbar < nit; ++nbar) lds_barrier();
+    };
+    if (w >= 2) role(std::true_type{});
+    else role(std::false_type{});
+  } else {
+    // ---- state waves ----
+    const int cw = w - NP, col = cw * kTile + li;
+    // Gbar columns col of all f rows: the sum over the later segments' pieces
+    f32x16 sacc[NRT];
+#pragma unroll
+    for (int rt = 0; rt < NRT; ++rt) sacc[rt] = f32x16{};
+    for (int sp = seg * ka.ppseg; sp < ka.npc; ++sp) {
+      const float* src = ka.dG + ((size_t)u * ka.npc + sp) * D * f + (size_t)col * f;
+#pragma unroll
+      for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+        for (int i = 0; i < 16; i += 4) {
+          const f32x4 y = *reinterpret_cast<const f32x4*>(src + rt * kTile + row_of(i, hh));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sacc[rt][i + e] += y[e];
+        }
+    }
+    // dL/dN^T of this wave's columns, a position ahead: the tokens
+    // row_of(8ks + e, hh) of column col
+    f32x4 graw[KL][2];
+    auto load_g = [&](int n) {
+      const float* src = ka.gnT + (((size_t)u * ka.nblk + blk_of(n)) * D + col) * kTile + 4 * hh;
+#pragma unroll
+      for (int ks = 0; ks < KL; ++ks) {
+        graw[ks][0] = *reinterpret_cast<const f32x4*>(src + 16 * ks);
+        graw[ks][1] = *reinterpret_cast<const f32x4*>(src + 16 * ks + 8);
+      }
+    };
+    // the rows of dvl through a buffer (the launcher keeps a unit's under
+    // 2 GiB): rows past the block length lie past its end and are dropped
+    const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(
+        ka.dvl + (size_t)u * T_ * D, 0, (int)((size_t)T_ * D * sizeof(float)), kBufferWord3);
+    const int vlane = row_ok ? (li * D + cw * kTile + 4 * hh) * (int)sizeof(float) : kPastBuffer;
+    const int krb0 = Tok::read_base(lane);
+    if (nb > 0) load_g(0);
+    lds_barrier();  // iterations -1 and 0: nothing to do yet
+    lds_barrier();
+    for (int n = 0; n < nb; ++n) {  // iteration n + 1
+      typename C::Buf& B = sh.buf[n & 1];
+      int krb = krb0;  // (opaque, as above)
+      asm volatile("" : "+v"(krb));
+      op_t gh[KL], gl[KL];
+#pragma unroll
+      for (int ks = 0; ks < KL; ++ks) split_op(graw[ks][0], graw[ks][1], gh[ks], gl[ks]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (n + 1 < nb) load_g(n + 1);
+      // readout: dvl = Gbar^T phi(k) against the blocks after this one; LDS
+      // operands in batches ahead of their products
+      f32x16 ol = {};
+      constexpr int KB = 4;
+#pragma unroll
+      for (int k0 = 0; k0 < C::KF; k0 += KB) {
+        op_t kh[KB], kl[KB];
+#pragma unroll
+        for (int j = 0; j < KB; ++j) {
+          kh[j] = lds_op_perm<bf16>(&B.phiK[0][li][0], k0 + j, hh, 0);
+          kl[j] = lds_op_perm<bf16>(&B.phiK[1][li][0], k0 + j, hh, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < KB; ++j) {
+          op_t sa, sl;
+          acc_op_pair(sacc[(k0 + j) / KL], (k0 + j) % KL, sa, sl);
+          ol = M::mma(sa, kh[j], ol);
+          ol = M::mma(sl, kh[j], ol);
+          ol = M::mma(sa, kl[j], ol);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      {
+        const int so = (int)((size_t)blk_of(n) * L * D * sizeof(float));
+#pragma unroll
+        for (int i = 0; i < 16; i += 4)
+          __builtin_amdgcn_raw_buffer_store_b128(
+              __builtin_bit_cast(u32x4, f32x4{ol[i], ol[i + 1], ol[i + 2], ol[i + 3]}), vrs,
+              vlane + 2 * i * (int)sizeof(float), so, 0);
+      }
+      // commit: Gbar += phi(Q)^T dL/dN (this wave's columns)
+#pragma unroll
+      for (int r0 = 0; r0 < NRT; r0 += 2) {
+        op_t ph[2][KL], pl[2][KL];
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+          for (int ks = 0; ks < KL; ++ks) {
+            ph[r][ks] = Tok::op(B.phiQ[0], krb, r0 + r, ks);
+            pl[r][ks] = Tok::op(B.phiQ[1], krb, r0 + r, ks);
+          }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < KL; ++ks)
+#pragma unroll
+          for (int r = 0; r < 2; ++r) {
+            sacc[r0 + r] = M::mma(ph[r][ks], gh[ks], sacc[r0 + r]);
+            sacc[r0 + r] = M::mma(ph[r][ks], gl[ks], sacc[r0 + r]);
+            sacc[r0 + r] = M::mma(pl[r][ks], gh[ks], sacc[r0 + r]);
+          }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      lds_barrier();
+    }
   }
 }
 
@@ -2545,13 +2813,14 @@ static hipError_t bwd_go(const BackwardArgs& a, hipStream_t st) {
   }
   // bf16 takes the pipelined forward walk (which also writes dL/du of the
   // queries when the input gradients are asked for); fp32 the four-wave one.
-  // The reverse walk with the input gradients is the four-wave one for both
-  // dtypes (it also writes dL/du of the keys and Gbar^T phi(K)).
+  // So with the reverse walk: on bf16 the pipelined one, and with the input
+  // gradients a second walk for Gbar^T phi(K); on fp32 the four-wave one, which
+  // does both.
+  // (the pipelined walks address a request's upstream rows, a unit's dL/dN^T
+  // and its rows of dvl through 32-bit buffer offsets)
+  const bool fits = (size_t)a.T * s.Hq * D * sizeof(T) < ((size_t)1 << 31) &&
+                    (size_t)ka.nblk * D * kTile * sizeof(float) < ((size_t)1 << 31);
   if constexpr (sizeof(T) == 2) {
-    // (the pipelined walk addresses a request's upstream rows and a unit's
-    // dL/dN^T through 32-bit buffer offsets)
-    const bool fits = (size_t)a.T * s.Hq * D * sizeof(T) < ((size_t)1 << 31) &&
-                      (size_t)ka.nblk * D * kTile * sizeof(float) < ((size_t)1 << 31);
     if (fits)
       hipLaunchKernelGGL((hyb_bwd_fpipe_kernel<D, F>), dim3(units * nseg), dim3(fpipe_threads<D>()),
                          0, st, ka);
@@ -2575,12 +2844,23 @@ static hipError_t bwd_go(const BackwardArgs& a, hipStream_t st) {
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (inputs) {
+  if constexpr (sizeof(T) == 2) {
+    if (inputs && !fits) {
+      hipLaunchKernelGGL((hyb_bwd_rev_kernel<T, D, F, true>), dim3(units * nseg), block, 0, st, ka, 0);
+    } else {
+      if (inputs) {
+        hipLaunchKernelGGL((hyb_bwd_rwalk_kernel<D, F, true>), dim3(units * nseg), dim3(rwalk_threads<D>()),
+                           0, st, ka);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL((hyb_bwd_dv_kernel<D, F>), dim3(units * nseg), dim3(dv_threads<D>()), 0, st, ka);
+      } else {
+        hipLaunchKernelGGL((hyb_bwd_rwalk_kernel<D, F, false>), dim3(units * nseg), dim3(rwalk_threads<D>()),
+                           0, st, ka);
+      }
+    }
+  } else if (inputs) {
     hipLaunchKernelGGL((hyb_bwd_rev_kernel<T, D, F, true>), dim3(units * nseg), block, 0, st, ka,
                        0);
-  } else if constexpr (sizeof(T) == 2) {
-    hipLaunchKernelGGL((hyb_bwd_rwalk_kernel<D, F>), dim3(units * nseg), dim3(rwalk_threads<D>()),
-                       0, st, ka);
   } else {
     hipLaunchKernelGGL((hyb_bwd_rev_kernel<T, D, F, false>), dim3(units * nseg), block, 0, st, ka,
                        0);

@@ -98,3 +98,20 @@ def test_train8_input_gradients_full():
     for x, r, what in zip(got[:3] + got[3:6], ref[3:] + ref[:3],
                           ("dq", "dk", "dv", "dW", "dalpha", "loss")):
         _close(x, r, "bf16", f"train8 {what}")
+
+
+EDGES = [
+    # the reverse walks and the input kernel at their edges: odd and single
+    # positions per segment, rows just short of a tile, groups of 1, 3 and 4
+    # heads, a short last segment
+    (2, 21, 6, 2, 64, 7, 32, "bf16"),
+    (1, 261, 4, 4, 128, 29, 32, "bf16"),
+    (3, 31, 8, 2, 64, 31, 64, "bf16"),
+    (1, 1056, 1, 1, 128, 32, 64, "bf16"),
+    (1, 93, 3, 1, 128, 31, 64, "f32"),
+]
+
+
+@pytest.mark.parametrize("shape", EDGES, ids=lambda s: "x".join(map(str, s)))
+def test_input_gradients_edges(shape):
+    test_input_gradients_match_oracle(shape, "dout")
