@@ -1530,11 +1530,17 @@ SegPlan segment_plan(const Shape& s, int T) {
 }
 
 // Workgroups of the walk and of the increments that the chip holds at once:
-// one per CU of the pipelined kernels (their LDS), two of the single-group
-// kernel, four at d = 64 (their registers).
+// one per CU, by the pipelined kernels' LDS and by the single-group kernel's
+// registers at d = 128 (four waves of one per SIMD); two at d = 64.
 static int prefill_fill(const Shape& s) {
-  if (s.dtype == 1 && s.F <= 64) return 256;
-  return s.D == 64 ? 1024 : 512;
+  return s.dtype == 1 && s.F <= 64 ? 256 : s.D == 64 ? 512 : 256;
+}
+
+// Rounds of n workgroups of the given steps, in steps: workgroups that share a
+// CU slow each other down (a fifth per neighbour).
+static float prefill_rounds(long n, int fill, float steps) {
+  const float share = (float)(n < fill ? n : fill) / 256.0f;
+  return (float)((n + fill - 1) / fill) * steps * (share > 1.0f ? 0.8f + 0.2f * share : 1.0f);
 }
 
 // The prefill's plan: the (segments, pieces per segment) with the least
@@ -1542,6 +1548,9 @@ static int prefill_fill(const Shape& s) {
 // In walk steps: rounds of walk workgroups times a segment's blocks and its
 // start (about 4); rounds of increment workgroups times a piece's blocks, at
 // 0.45 of a step each, and their start (about 2); and the two launches (4).
+// (Counting two of the fp32 kernel's workgroups per CU at d = 128, where its
+// registers let one in, took 4 x 2048 tokens from 1112 to 1318 us; as counted
+// here they take 1069 us.)
 // With up to 8 segments, as the backward's, one prompt of 16384 tokens walks
 // on 128 CUs: 240 us, against 126 us with the 16 segments chosen here (2 of
 // 8192: 162 and 125, 4 of 2048: 99 and 79, 1 of 1024: 66 and 35).
@@ -1550,7 +1559,7 @@ SegPlan prefill_plan(const Shape& s, int T) {
   const int fill = prefill_fill(s);
   SegPlan best;
   best.sb = best.pb = nblk;
-  float least = (float)((units + fill - 1) / fill) * (nblk + 4);
+  float least = prefill_rounds(units, fill, (float)(nblk + 4));
   SegPlan p;
   for (p.nseg = 2; p.nseg <= room + 1 && p.nseg <= nblk; ++p.nseg) {
     p.sb = (nblk + p.nseg - 1) / p.nseg;
@@ -1559,8 +1568,8 @@ SegPlan prefill_plan(const Shape& s, int T) {
       p.pb = (p.sb + p.ppseg - 1) / p.ppseg;
       if ((p.ppseg - 1) * p.pb >= p.sb) continue;  // every piece non-empty
       const long wg = (long)units * p.nseg, dg = (long)units * p.npieces();
-      const float cost = (float)((wg + fill - 1) / fill) * (float)(p.sb + 4) +
-                         (float)((dg + fill - 1) / fill) * (0.45f * (float)p.pb + 2.0f) + 4.0f;
+      const float cost = prefill_rounds(wg, fill, (float)(p.sb + 4)) +
+                         prefill_rounds(dg, fill, 0.45f * (float)p.pb + 2.0f) + 4.0f;
       if (cost < least) {
         least = cost;
         best = p;
