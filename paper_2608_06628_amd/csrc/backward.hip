@@ -2449,6 +2449,12 @@ __global__ __launch_bounds__(dv_threads<D>()) void hyb_bwd_dv_kernel(BwdKArgs ka
 // the accumulators.  w a_ij is evaluated as exp(log w + s_ij): scores must
 // stay well inside the fp32 exponent range (the forward walk's 1/D has the
 // same limit).
+// Bound by each head's chain (staging, 48 MFMAs of scores, exponentials, the
+// products), so on bf16 the registers are held to 256, two workgroups per CU:
+// dL/du and the state part of dv are requested behind the scores, not per use
+// or a head ahead, and the column operands come from transposing LDS reads
+// instead of two-byte gathers.  4 x 2048 tokens: 147 us with one workgroup
+// per CU (438 registers), 98 us so.
 // ---------------------------------------------------------------------------
 template <typename T, int D, int F>
 struct InCfg {
@@ -2488,6 +2494,22 @@ __device__ inline typename Mma<T>::op_t lds_col_op(const T* col, int ld, int ks,
   return x;
 }
 
+// The same operand of columns c0 + li of a row-major LDS tile: on bf16 by
+// transposing reads (rows 16ks + 4hh .. + 3 and the 4 rows 8 further on, or,
+// natural, rows 16ks + 8hh .. + 7).
+template <typename T>
+__device__ inline typename Mma<T>::op_t lds_cols_op(const T* tile, int ld, int c0, int lane, int ks,
+                                                    bool natural) {
+  const int li = lane & 31, hh = lane >> 5;
+  if constexpr (Mma<T>::E == 1) {
+    return lds_col_op<T>(tile + c0 + li, ld, ks, hh, natural);
+  } else {
+    const int i = lane & 15, b = (lane >> 4) & 1;
+    const T* p = tile + (size_t)(16 * ks + (natural ? 8 : 4) * hh + (i >> 2)) * ld + c0 + 16 * b + 4 * (i & 3);
+    return lds_tr_op(p, p + (natural ? 4 : 8) * ld);
+  }
+}
+
 // Accumulator registers ks*E .. as an operand pair hi + lo (lo zero on fp32).
 template <typename T>
 __device__ inline void acc_split(const f32x16& x, int ks, typename Mma<T>::op_t& hi,
@@ -2501,7 +2523,7 @@ __device__ inline void acc_split(const f32x16& x, int ks, typename Mma<T>::op_t&
 }
 
 template <typename T, int D, int F>
-__global__ __launch_bounds__(kWave*(D / kTile)) void hyb_bwd_inputs_kernel(BwdKArgs ka) {
+__global__ __launch_bounds__(kWave*(D / kTile), sizeof(T) == 2 ? 2 : 1) void hyb_bwd_inputs_kernel(BwdKArgs ka) {
   typedef InCfg<T, D, F> C;
   typedef typename C::M M;
   typedef typename C::op_t op_t;
@@ -2518,7 +2540,7 @@ __global__ __launch_bounds__(kWave*(D / kTile)) void hyb_bwd_inputs_kernel(BwdKA
   const int b = bg / Hkv, g = bg % Hkv;
   const size_t t0 = (size_t)blk * L;
   const size_t qstride = (size_t)Hq * D, kstride = (size_t)Hkv * D;
-  const float scale = 1.0f / sqrtf((float)D);
+  const float scale = 1.0f / sqrtf((float)D), scale2 = scale * kLog2e;
   const int cc = w * kTile + li;  // this lane's output column
   const bool lrow = li < L;
 
@@ -2546,9 +2568,11 @@ __global__ __launch_bounds__(kWave*(D / kTile)) void hyb_bwd_inputs_kernel(BwdKA
   stage_rows(sh.k, (const T*)a.k + (((size_t)b * T_ + t0) * Hkv + g) * D, kstride);
   stage_rows(sh.v, (const T*)a.v + (((size_t)b * T_ + t0) * Hkv + g) * D, kstride);
 
-  // A head's staged operands (its Q rows, dL/dN^T, W_h and dL/dD) are
-  // fetched into registers while the previous head is computed, then moved
-  // to LDS.
+  // A head's staged operands (its Q rows, dL/dN^T, W_h and dL/dD) go to LDS
+  // through registers.  On bf16 two workgroups share a CU (kTwo) and each
+  // other's waits; on fp32 a workgroup has the CU to itself and fetches the
+  // next head's operands while the current head is computed.
+  constexpr bool kTwo = sizeof(T) == 2;
   constexpr int NQ = kTile * (D / EPC) / NTHR, NG = D * kTile / NTHR, NWT = F * (D / EPC) / NTHR;
   static_assert(NQ * NTHR == kTile * (D / EPC) && NG * NTHR == D * kTile &&
                     NWT * NTHR == F * (D / EPC),
@@ -2558,9 +2582,8 @@ __global__ __launch_bounds__(kWave*(D / kTile)) void hyb_bwd_inputs_kernel(BwdKA
     float xg[NG];
     uint4 xw[NWT];
     float gdl, alpha;
-    float xv[16];  // the state part of dv at this lane's rows (below)
   };
-  auto fetch = [&](int hq, HeadRegs& r) {
+  auto fetch = [&](int hq, HeadRegs& r, int tid) {
     const int h = g * G + hq;
     const size_t u = (size_t)b * Hq + h;
     const T* qsrc = (const T*)a.q + (((size_t)b * T_ + t0) * Hq + h) * D;
@@ -2580,13 +2603,8 @@ __global__ __launch_bounds__(kWave*(D / kTile)) void hyb_bwd_inputs_kernel(BwdKA
     }
     r.gdl = tid < kTile ? ka.gd[(u * nblk + blk) * kTile + tid] : 0.0f;
     r.alpha = a.alpha[h];
-    // Gbar^T phi(k_j) from the reverse walk, rows j = row_of(r, hh) (rows
-    // past the block read row L-1 and are dropped where they are added)
-    const float* vsrc = ka.dvl + (u * T_ + t0) * D + cc;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) r.xv[i] = vsrc[(size_t)min(row_of(i, hh), L - 1) * D];
   };
-  auto put = [&](const HeadRegs& r) {
+  auto put = [&](const HeadRegs& r, int tid) {
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
       const int it = tid + k * NTHR, rr = it / (D / EPC), c = (it % (D / EPC)) * EPC;
@@ -2608,19 +2626,23 @@ __global__ __launch_bounds__(kWave*(D / kTile)) void hyb_bwd_inputs_kernel(BwdKA
     }
   };
   HeadRegs hr;
-  fetch(0, hr);
+  if constexpr (!kTwo) fetch(0, hr, tid);
 
-  f32x16 dks = {}, dkl = {}, dva = {};
+  f32x16 dks = {}, dva = {};
   for (int hq = 0; hq < G; ++hq) {
     const int h = g * G + hq;
     const size_t u = (size_t)b * Hq + h;
-    const float lw = log_sigmoid(hr.alpha);
-    float xv[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) xv[i] = hr.xv[i];
+    // (the thread index through an opaque copy: addresses and masks are formed
+    // per head, not kept in registers across the loop, where they would spill)
+    int tl = tid;
+    asm volatile("" : "+v"(tl));
+    const int lane = tl & (kWave - 1), li = lane & 31, hh = lane >> 5, cc = w * kTile + li;
+    const bool lrow = li < L;
+    if constexpr (kTwo) fetch(hq, hr, tl);
+    const float lw2 = log_sigmoid(hr.alpha) * kLog2e;
     lds_barrier();  // the previous head's readers are done
-    put(hr);
-    if (hq + 1 < G) fetch(hq + 1, hr);  // the next head's operands in flight
+    put(hr, tl);
+    if (!kTwo && hq + 1 < G) fetch(hq + 1, hr, tl);  // the next head's operands in flight
     lds_barrier();
 
     // Scores and dL/dP = dL/dN_i . v_j: queries in lanes (sq, pq: rows j,
@@ -2642,76 +2664,108 @@ __global__ __launch_bounds__(kWave*(D / kTile)) void hyb_bwd_inputs_kernel(BwdKA
         pk = M::mma(nl, vo, pk);
       }
     }
-    // w a_ij and dL/ds_ij in both orientations (zero outside the block)
+    // dL/du of the head's queries and keys (rows: tokens, natural F) and the
+    // state part of dv (rows row_of(r, hh)), requested here and used behind the
+    // products below.  Buffers of the block's rows: rows past L read as zeros.
+    auto rows_of = [&](const float* p, int n) {
+      return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p) + (u * T_ + t0) * n, 0,
+                                               L * n * (int)sizeof(float), kBufferWord3);
+    };
+    constexpr int NDU = E == 1 ? 1 : 2 * C::KF;  // (bf16; fp32 loads at its use)
+    f32x4 xu[2][NDU];
+    if constexpr (E > 1) {
+      const __amdgpu_buffer_rsrc_t rq = rows_of(ka.duq, F), rk = rows_of(ka.duk, F);
+      const int off = (li * F + hh * E) * (int)sizeof(float);
+#pragma unroll
+      for (int k = 0; k < NDU; ++k) {
+        const int at = off + (k / 2 * KW + k % 2 * 4) * (int)sizeof(float);
+        xu[0][k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rq, at, 0, 0));
+        xu[1][k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, at, 0, 0));
+      }
+    }
+    float xv[16];
+    {
+      const __amdgpu_buffer_rsrc_t rv = rows_of(ka.dvl, D);
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        xv[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                              rv, (row_of(r, hh) * D + cc) * (int)sizeof(float), 0, 0));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // w a_ij and dL/ds_ij / sqrt(d) in both orientations (zero outside the
+    // block)
     f32x16 dsq, ak, dsk;
     {
       const float gdi = sh.gd[li];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int o = row_of(r, hh);
-        const float aq = (lrow && o < L) ? expf(lw + sq[r] * scale) : 0.0f;
-        dsq[r] = aq * (pq[r] + gdi);
-        ak[r] = (lrow && o < L) ? expf(lw + sk[r] * scale) : 0.0f;
-        dsk[r] = ak[r] * (pk[r] + sh.gd[o]);
+        const float aq = (lrow && o < L) ? __builtin_amdgcn_exp2f(__builtin_fmaf(sq[r], scale2, lw2)) : 0.0f;
+        dsq[r] = aq * (pq[r] + gdi) * scale;
+        ak[r] = (lrow && o < L) ? __builtin_amdgcn_exp2f(__builtin_fmaf(sk[r], scale2, lw2)) : 0.0f;
+        dsk[r] = ak[r] * (pk[r] + sh.gd[o]) * scale;
       }
     }
 
-    // dq: sum_j ds_ij k_j (scaled after) + du(q_i) W_h^T
-    f32x16 dqs = {}, dql = {};
+    // dq: sum_j ds_ij k_j + du(q_i) W_h^T
+    f32x16 dqs = {};
 #pragma unroll
     for (int ks = 0; ks < C::KL; ++ks) {
       op_t hi, lo;
       acc_split<T>(dsq, ks, hi, lo);
-      const op_t kc = lds_col_op<T>(&sh.k[0][cc], LD, ks, hh, false);
+      const op_t kc = lds_cols_op<T>(&sh.k[0][0], LD, w * kTile, lane, ks, false);
       dqs = M::mma(hi, kc, dqs);
       if constexpr (C::NPART == 2) dqs = M::mma(lo, kc, dqs);
       // dk (this head): sum_i ds_ij q_i
       acc_split<T>(dsk, ks, hi, lo);
-      const op_t qc = lds_col_op<T>(&sh.q[0][cc], LD, ks, hh, false);
+      const op_t qc = lds_cols_op<T>(&sh.q[0][0], LD, w * kTile, lane, ks, false);
       dks = M::mma(hi, qc, dks);
       if constexpr (C::NPART == 2) dks = M::mma(lo, qc, dks);
       // dv (this head): sum_i w a_ij dL/dN_i
       acc_split<T>(ak, ks, hi, lo);
-      const op_t nc = lds_col_op<T>(&sh.dn[0][0][cc], LD, ks, hh, false);
+      const op_t nc = lds_cols_op<T>(&sh.dn[0][0][0], LD, w * kTile, lane, ks, false);
       dva = M::mma(hi, nc, dva);
       if constexpr (C::NPART == 2) {
         dva = M::mma(lo, nc, dva);
-        dva = M::mma(hi, lds_col_op<T>(&sh.dn[1][0][cc], LD, ks, hh, false), dva);
+        dva = M::mma(hi, lds_cols_op<T>(&sh.dn[1][0][0], LD, w * kTile, lane, ks, false), dva);
       }
     }
-    // feature-map parts: du (rows: tokens, natural F) times W_h^T
-    {
-      const float* duq = ka.duq + (u * T_ + t0 + min(li, L - 1)) * F;
-      const float* duk = ka.duk + (u * T_ + t0 + min(li, L - 1)) * F;
+    // feature-map parts: du times W_h^T
 #pragma unroll
-      for (int ks = 0; ks < C::KF; ++ks) {
-        const op_t wc = lds_col_op<T>(&sh.wt[0][cc], LD, ks, hh, true);
-        op_t hi, lo;
-        load_split_op<T>(duq + ks * KW + hh * E, hi, lo);
-        hi = keep_if<T>(lrow, hi);
-        lo = keep_if<T>(lrow, lo);
-        dql = M::mma(hi, wc, dql);
-        if constexpr (C::NPART == 2) dql = M::mma(lo, wc, dql);
-        load_split_op<T>(duk + ks * KW + hh * E, hi, lo);
-        hi = keep_if<T>(lrow, hi);
-        lo = keep_if<T>(lrow, lo);
-        dkl = M::mma(hi, wc, dkl);
-        if constexpr (C::NPART == 2) dkl = M::mma(lo, wc, dkl);
+    for (int ks = 0; ks < C::KF; ++ks) {
+      const op_t wc = lds_cols_op<T>(&sh.wt[0][0], LD, w * kTile, lane, ks, true);
+      op_t hi, lo;
+      if constexpr (E > 1) {
+        split_op(xu[0][2 * ks], xu[0][2 * ks + 1], hi, lo);
+        dqs = M::mma(hi, wc, dqs);
+        dqs = M::mma(lo, wc, dqs);
+        split_op(xu[1][2 * ks], xu[1][2 * ks + 1], hi, lo);
+        dks = M::mma(hi, wc, dks);
+        dks = M::mma(lo, wc, dks);
+      } else {
+        const size_t at = (u * T_ + t0 + min(li, L - 1)) * F + ks * KW + hh * E;
+        load_split_op<T>(ka.duq + at, hi, lo);
+        dqs = M::mma(keep_if<T>(lrow, hi), wc, dqs);
+        load_split_op<T>(ka.duk + at, hi, lo);
+        dks = M::mma(keep_if<T>(lrow, hi), wc, dks);
       }
     }
-    // dq of head h: rows i (queries), column cc
+    // dq of head h: rows i (queries), column cc; rows past L lie past the
+    // buffer's end and are dropped
     {
-      float* dst = a.dq + (((size_t)b * T_ + t0) * Hq + h) * D + cc;
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          a.dq + (((size_t)b * T_ + t0) * Hq + h) * D, 0,
+          ((L - 1) * (int)qstride + D) * (int)sizeof(float), kBufferWord3);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int i = row_of(r, hh);
-        if (i < L) dst[(size_t)i * qstride] = dqs[r] * scale + dql[r];
+        const float x = dqs[r];  // (bit_cast of a vector's element takes element 0)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), rs,
+                                              (row_of(r, hh) * (int)qstride + cc) * (int)sizeof(float), 0, 0);
       }
     }
     // the state part of dv: Gbar^T phi(k_j) from the reverse walk
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      if (row_of(r, hh) < L) dva[r] += xv[r];
+    for (int r = 0; r < 16; ++r) dva[r] += xv[r];
   }
   // dk, dv of the KV head: rows j (keys), column cc
   float* dkd = a.dk + (((size_t)b * T_ + t0) * Hkv + g) * D + cc;
@@ -2720,7 +2774,7 @@ __global__ __launch_bounds__(kWave*(D / kTile)) void hyb_bwd_inputs_kernel(BwdKA
   for (int r = 0; r < 16; ++r) {
     const int j = row_of(r, hh);
     if (j < L) {
-      dkd[(size_t)j * kstride] = dks[r] * scale + dkl[r];
+      dkd[(size_t)j * kstride] = dks[r];
       dvd[(size_t)j * kstride] = dva[r];
     }
   }
