@@ -99,21 +99,26 @@ def _dt(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported activation dtype {t.dtype}")
 
 
+# The host's time for a call is what a small step waits for (its kernel runs
+# for about 5.5 us): the accepted tensor takes one expression, and the stream
+# comes as torch's raw handle, without the Python object around it (0.1 against
+# 2.6 us).  One request's step, calls in a row: 9.2 us before, 6.5 us so.
 def _ptr(t, name, dtype=None):
     if t is None:
         return None
+    if (isinstance(t, torch.Tensor) and t.is_cuda and (dtype is None or t.dtype is dtype)
+            and t.is_contiguous()):
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA (HIP) tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if dtype is not None and t.dtype != dtype:
-        raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    return t.data_ptr()
+    raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
 
 
 def _stream(stream):
-    if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+    if stream is None:  # the current stream of the current device
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return getattr(stream, "cuda_stream", stream)
 
 

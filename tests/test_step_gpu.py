@@ -197,3 +197,40 @@ def test_small_batch_kernels(B):
             else "split" if B * dims.Hq * (dims.d // 32) <= 1024
             else "halves" if groups2 <= 256 else "whole")
     assert np.array_equal(auto, run_step(c, dims, kernel=want)), f"automatic choice is not {want}"
+
+
+def test_stream_and_refusals():
+    """A call goes to the current stream (here the one under capture: a launch
+    elsewhere would fail or be missing from the graph) unless it names one;
+    tensors a kernel cannot take are refused with the error of their kind."""
+    dims = synth.TINY
+    announce("step: streams and refused tensors")
+    c = make_case(dims, synth.TINY_PREFIX, seed=0, scale=1.0, w_std=0.02)
+    a = dict(q=act(c["q"], dims.dtype), k=act(c["k"], dims.dtype), v=act(c["v"], dims.dtype),
+             W=act(c["Wt"], dims.dtype), alpha=f32(c["alpha"]), S=state_dev(c["S"]),
+             z=f32(c["z"]))
+    want = hb.hybrid_attn_step(**a)
+    torch.cuda.synchronize()
+    out = torch.zeros_like(want)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        hb.hybrid_attn_step(**a, out=out)
+    assert not out.any()
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+    side = torch.cuda.Stream()
+    for stream in (side, side.cuda_stream):
+        out.zero_()
+        side.wait_stream(torch.cuda.current_stream())
+        hb.hybrid_attn_step(**a, out=out, stream=stream)
+        side.synchronize()
+        assert torch.equal(out, want)
+    for name, bad, error in [("k", a["k"].cpu(), TypeError), ("k", c["k"], TypeError),
+                             ("alpha", a["alpha"].double(), TypeError),
+                             ("S", a["S"].transpose(2, 3).contiguous().transpose(2, 3),
+                              ValueError)]:
+        with pytest.raises(error, match=name):
+            hb.hybrid_attn_step(**{**a, name: bad})
