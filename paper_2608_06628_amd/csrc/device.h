@@ -151,21 +151,6 @@ __device__ inline float cvt_op<float>(const float* x) {
 }
 
 // x, or a zero operand when ok is false (a select, not a branch).
-// Accumulator registers ks*E .. ks*E+E-1 as a T operand; the tile's rows
-// become the contraction index (row_of order).  For values that a T holds
-// exactly (a transpose through the identity).
-template <typename T>
-__device__ inline typename Mma<T>::op_t acc_op_exact(const f32x16& x, int ks) {
-  typename Mma<T>::op_t r;
-  if constexpr (Mma<T>::E == 1) {
-    r = x[ks];
-  } else {
-#pragma unroll
-    for (int e = 0; e < Mma<T>::E; ++e) r[e] = (T)x[ks * Mma<T>::E + e];
-  }
-  return r;
-}
-
 template <typename T>
 __device__ inline typename Mma<T>::op_t keep_if(bool ok,
                                                typename Mma<T>::op_t x) {
@@ -279,21 +264,6 @@ __device__ inline void store_out8_nt(void* out, size_t idx, const float* v,
                    (bf16)v[4], (bf16)v[5], (bf16)v[6], (bf16)v[7]};
     __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(&x),
                                 reinterpret_cast<u32x4*>((bf16*)out + idx));
-  }
-}
-
-// Eight consecutive outputs at element index idx (16-byte aligned): fp32 as
-// two 16-byte stores, bf16 as one.
-template <typename T>
-__device__ inline void store_out8(void* out, size_t idx, const float* v, bool f32) {
-  if (sizeof(T) == 4 || f32) {
-    f32x4* o = reinterpret_cast<f32x4*>((float*)out + idx);
-    o[0] = f32x4{v[0], v[1], v[2], v[3]};
-    o[1] = f32x4{v[4], v[5], v[6], v[7]};
-  } else {
-    *reinterpret_cast<bf16x8*>((bf16*)out + idx) =
-        bf16x8{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3],
-               (bf16)v[4], (bf16)v[5], (bf16)v[6], (bf16)v[7]};
   }
 }
 
