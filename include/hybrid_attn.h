@@ -182,8 +182,7 @@ int hybrid_state_commit(const hyb_dims_t* dims, const void* k, const void* v,
  * is then ignored and may be NULL).  ws/ws_bytes: workspace of at least
  * hybrid_workspace_bytes(dims, HYB_OP_PREFILL, seq_len) bytes (may be NULL
  * when that is 0); the prompt is processed in sequence segments whose state
- * increments (and a snapshot of the incoming state, which the segments start
- * from) pass through it, so results equal the block-by-block ones up to the
+ * increments (and the states the segments start from) pass through it, so results equal the block-by-block ones up to the
  * order of fp32 additions.  It must not overlap any other argument.  Two
  * requests of one call must not share a slot. */
 int hybrid_state_prefill(const hyb_dims_t* dims, int32_t seq_len,
