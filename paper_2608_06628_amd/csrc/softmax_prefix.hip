@@ -200,6 +200,41 @@ __device__ inline float* sp_ml(const SoftmaxPrefixArgs& a) {
   return (float*)a.ws + (size_t)a.s.B * a.n_split * a.s.Hq * a.s.L * D;
 }
 
+// The reference of a query's weights 2^(s - ref), in the log2 domain.  P enters
+// P V rounded to bf16, and a weight that is a power of two does not round; so
+// the heaviest weights, those that make a row, round least if the references
+// have the fractions of the maxima of many tiles.  With one running maximum per
+// range the error therefore grows with the range's length (rms of the weights'
+// part over 512, 8224 and 32800 normal keys: 1.42, 1.59 and 1.63e-3).  So a tile
+// may restart the reference at its own maximum, moved up by whole powers of two
+// to at least the maximum so far (no accumulator grows), and in between a
+// larger maximum raises it.  A restart costs a rescale of the accumulators.
+// Where a maximum is young, tiles rescale anyway (some of a wave's 32 queries
+// rises in two of three tiles up to the 32nd): there every tile restarts, later
+// every fourth (1.17 and 1.54e-3: less than any range of a quarter or an eighth of
+// the length, which is how much shorter equal cuts of the longest prefix are).
+// Error against 64 bits, bf16 outputs included, and time of 128 x 32768 keys:
+// 2.25e-3 and 1531 us, with one running maximum per range 2.32e-3 and 1528 us,
+// with a restart at every tile throughout 2.1e-3 and 1710 us; 24 paged requests
+// of 1 to 8192: 2.0e-3 and 70 us, and 2.2e-3 and 71 us.
+struct SpRef {
+  float most = -INFINITY;  // maximum so far
+  float ref = -INFINITY;
+  __device__ static inline bool restarts(int n) { return n < 64 || n % 4 == 0; }
+  // Takes tile n's maximum; true where some lane's reference moves, to next
+  // (what it was is left in ref for the rescale, and set by the caller).
+  __device__ inline bool take(float mt, int n, float& next) {
+    most = fmaxf(most, mt);
+    if (restarts(n)) {  // uniform
+      const float w = fmaxf(mt, most - 100.0f);  // (finite after a finite tile)
+      next = w + fmaxf(0.0f, ceilf(most - w));
+    } else {
+      next = fmaxf(ref, mt);
+    }
+    return __any(next != ref);
+  }
+};
+
 // One wave per query head of the KV group; 32-key tiles double-buffered in
 // LDS: the tile after next is loaded into registers while the current one is
 // computed, and the next one is moved from registers into the free buffer at
@@ -307,8 +342,13 @@ __global__ __launch_bounds__(kWave* NG) void hyb_sp_partial_kernel(
     }
   };
 
-  const float scale = 1.0f / sqrtf((float)D);
-  float m = -INFINITY, l = 0.0f;
+  // Scores are scaled by 1/sqrt(d) and, on bf16, kept in the log2 domain of
+  // SpRef (fp32 weights do not round, and keep one running maximum).
+  constexpr bool kWin = sizeof(T) == 2;
+  const float scale = (kWin ? kLog2e : 1.0f) / sqrtf((float)D);
+  SpRef rf;
+  float& m = rf.ref;
+  float l = 0.0f;
   f32x16 acc[C::NCT];
 #pragma unroll
   for (int ct = 0; ct < C::NCT; ++ct) acc[ct] = f32x16{};
@@ -339,18 +379,26 @@ __global__ __launch_bounds__(kWave* NG) void hyb_sp_partial_kernel(
       mt = fmaxf(mt, p[i]);
     }
     mt = fmaxf(mt, xor32(mt));
-    const float mn = fmaxf(m, mt);
+    float mn;
+    bool moves;
+    if constexpr (kWin) {
+      moves = rf.take(mt, n, mn);
+    } else {
+      mn = fmaxf(m, mt);
+      moves = __any(mn > m);
+    }
+    auto ex = [](float x) { return kWin ? __builtin_amdgcn_exp2f(x) : fast_exp(x); };
     float ps = 0.0f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      p[i] = as_operand<T>(fast_exp(p[i] - mn));  // exp(-inf) = 0 past the range
+      p[i] = as_operand<T>(ex(p[i] - mn));  // exp(-inf) = 0 past the range
       ps += p[i];
     }
     ps += xor32(ps);
-    // The accumulators are rescaled only when some query's running maximum
-    // rose: once the maximum settles most tiles skip the 64 multiplies.
-    if (__any(mn > m)) {
-      const float corr = fast_exp(m - mn);
+    // The accumulators are rescaled only when some query's reference moved:
+    // once the maximum settles most tiles skip the 64 multiplies.
+    if (moves) {
+      const float corr = ex(m - mn);
       l *= corr;
 #pragma unroll
       for (int ct = 0; ct < C::NCT; ++ct)
@@ -395,7 +443,7 @@ __global__ __launch_bounds__(kWave* NG) void hyb_sp_partial_kernel(
       *reinterpret_cast<f32x4*>(wacc + ct * kTile + row_of(i, hh)) =
           f32x4{acc[ct][i], acc[ct][i + 1], acc[ct][i + 2], acc[ct][i + 3]};
   if (hh == 0) {
-    wml[0] = m;
+    wml[0] = kWin ? m * 0.6931471805599453f : m;  // (the natural log)
     wml[1] = l;
   }
 }
@@ -561,7 +609,7 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
     }
   };
 
-  // Scores and the running maximum m are kept in the log2 domain (scaled by
+  // Scores and the reference m (SpRef) are kept in the log2 domain (scaled by
   // log2 e with 1/sqrt(d)), so each weight is one fma and one exp2;
   // m is converted back where it is written out for the combine.
   const float scale = 1.4426950408889634f / sqrtf((float)D);
@@ -572,7 +620,8 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
   // is one on the quarters of the parity of x / 4, which is that of the lane
   // that receives the row, so register 0 is the sum of the lane's own query
   // (only that register is kept rescaled).
-  float m = -INFINITY;
+  SpRef rf;
+  float& m = rf.ref;
   f32x16 acc[NCT];
   f32x4 lsum = {};
 #pragma unroll
@@ -586,13 +635,13 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
     const int c = 2 * ks + hh;  // 16-byte chunk of elements ks*KW + hh*E
     return load_op<bf16>(&kt[li * D + (c ^ RG::swz(li)) * EPC]);
   };
-  // Scores of the tile of the current step, already in the running maximum
-  // (and the accumulators rescaled to it).
+  // Scores of the tile of the current step, already in the reference (and the
+  // accumulators rescaled to it).
   f32x16 sc;
-  // Takes the scores of tile n into sc and the running maximum.  The
-  // accumulators are rescaled only when some query's maximum rose: once the
-  // maximum settles most tiles skip the 64 multiplies.  Keys past the range,
-  // in the range's last tile only, are masked.
+  // Takes the scores of tile n into sc and the reference.  The accumulators are
+  // rescaled only when some query's reference moved: once the maximum settles
+  // most tiles skip the 64 multiplies.  Keys past the range, in the range's
+  // last tile only, are masked.
   auto take_scores = [&](auto check, int n, const f32x16& s) __attribute__((always_inline)) {
     sc = s;
     if constexpr (decltype(check)::value) {
@@ -606,8 +655,8 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
 #pragma unroll
     for (int i = 1; i < 16; ++i) mt = fmaxf(mt, sc[i]);
     mt = fmaxf(mt, xor32(mt));
-    const float mn = fmaxf(m, mt * scale);
-    if (__any(mn > m)) {
+    float mn;
+    if (rf.take(mt * scale, n, mn)) {
       const float corr = __builtin_amdgcn_exp2f(m - mn);
       lsum[0] *= corr;
 #pragma unroll

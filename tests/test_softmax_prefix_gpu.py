@@ -109,3 +109,48 @@ def test_softmax_prefix_mixed_lengths(case):
                                      out_f32=True)
     torch.cuda.synchronize()
     assert torch.equal(a, b)
+
+
+def _weights_error(q, k, v, P, splits):
+    """The attention of q [B][L][Hq][d] over k, v [B][N][Hkv][d] in 64 bits, and
+    the same with bf16 weights relative to the running maximum, tile by tile of
+    32 keys, of `splits` equal cuts of the keys (whole tiles)."""
+    B, L, Hq, d = q.shape
+    N, Hkv = k.shape[1:3]
+    G = Hq // Hkv
+    qh = q.double().permute(0, 2, 1, 3).reshape(B, Hkv, G * L, d)
+    kh, vh = (x.double().permute(0, 2, 1, 3) for x in (k, v))
+    s = torch.matmul(qh, kh.transpose(-1, -2).contiguous()) * (np.log2(np.e) / np.sqrt(d))
+    exact = torch.matmul(torch.softmax(s * np.log(2.0), -1), vh)
+    cut = -(-(-(-N // splits)) // 32) * 32
+    num, den = 0.0, 0.0
+    for lo in range(0, N, cut):
+        x = s[..., lo:lo + cut]
+        run = torch.nn.functional.pad(x, (0, -x.shape[-1] % 32), value=-1e30)
+        run = run.unflatten(-1, (-1, 32)).amax(-1).cummax(-1).values
+        ref = run.repeat_interleave(32, -1)[..., :x.shape[-1]]
+        p = torch.exp2(x - ref).float().to(torch.bfloat16).double() * torch.exp2(ref - s.amax(-1, True))
+        num, den = num + torch.matmul(p, vh[:, :, lo:lo + cut]), den + p.sum(-1, True)
+    back = lambda x: x.reshape(B, Hq, L, d).permute(0, 2, 1, 3)
+    return back(exact), back(num / den)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,P", [(16, 32, 32, 4, 4096), (32, 48, 16, 4, 4096)],
+                         ids=["ring", "staged"])
+def test_softmax_prefix_long_ranges_round_no_worse(B, Hq, Hkv, L, P):
+    """The rounding of the weights to bf16 costs no more than with the equal
+    cuts of the longest prefix into up to 2048 workgroups, however long the
+    ranges of a call that needs fewer are."""
+    d = 64
+    announce(f"softmax_prefix rounding of long ranges {B}x{Hq}x{Hkv}x{P}")
+    g = torch.Generator(device="cuda").manual_seed(301)
+    rnd = lambda *n: torch.randn(n, generator=g, device="cuda").to(torch.bfloat16)
+    q, k, v = rnd(B, L, Hq, d), rnd(B, L, Hkv, d), rnd(B, L, Hkv, d)
+    kc, vc = rnd(B, P, Hkv, d), rnd(B, P, Hkv, d)
+    out = hb.softmax_prefix_step(q, k, v, kc, vc, i32([P] * B), out_f32=True)
+    splits = max(1, min(-(-2048 // (B * Hkv)), -(-(P + L) // 512)))
+    exact, cuts = _weights_error(q, torch.cat([kc, k], 1), torch.cat([vc, v], 1), P, splits)
+    rms = lambda x: float((x - exact).square().mean().sqrt() / exact.square().mean().sqrt())
+    here, bound = rms(out.double()), rms(cuts)
+    print(f"[rounding] {here:.3e}, equal cuts {bound:.3e}")
+    assert here <= bound
