@@ -154,3 +154,28 @@ def test_softmax_prefix_long_ranges_round_no_worse(B, Hq, Hkv, L, P):
     here, bound = rms(out.double()), rms(cuts)
     print(f"[rounding] {here:.3e}, equal cuts {bound:.3e}")
     assert here <= bound
+
+
+def test_softmax_prefix_time_per_request_is_constant():
+    """A request's time in a call of many short ones does not grow with their
+    number (every workgroup once walked all lengths: 4 times the bound here)."""
+    Hkv, d, L, P = 8, 64, 4, 32
+    announce("softmax_prefix time per request")
+    us = {}
+    for B in (512, 8192):
+        x = torch.randn((B, P, Hkv, d), device="cuda").to(torch.bfloat16)
+        args = (x[:, :L].contiguous(),) * 3 + (x, x, i32([P] * B))
+        out = hb.softmax_prefix_step(*args)
+        best = float("inf")
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            torch.cuda._sleep(200000)
+            a.record()
+            for _ in range(5):
+                hb.softmax_prefix_step(*args, out=out)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 200)
+        us[B] = best
+    print(f"[time] {us}")
+    assert us[8192] <= 2 * 16 * us[512]
