@@ -218,6 +218,8 @@ __device__ inline float* sp_ml(const SoftmaxPrefixArgs& a) {
 // rises in two of three tiles up to the 32nd): there every tile restarts, later
 // every fourth (1.17 and 1.54e-3: less than any range of a quarter or an eighth of
 // the length, which is how much shorter equal cuts of the longest prefix are).
+// The register-staged kernel, which waits for its own arithmetic, restarts at
+// every second of the early tiles (1.41e-3).
 // Error against 64 bits, bf16 outputs included, and time of 128 x 32768 keys:
 // 2.25e-3 and 1531 us, with one running maximum per range 2.32e-3 and 1528 us,
 // with a restart at every tile throughout 2.1e-3 and 1710 us; 24 paged requests
@@ -225,12 +227,13 @@ __device__ inline float* sp_ml(const SoftmaxPrefixArgs& a) {
 struct SpRef {
   float most = -INFINITY;  // maximum so far
   float ref = -INFINITY;
-  __device__ static inline bool restarts(int n) { return n < 64 || n % 4 == 0; }
-  // Takes tile n's maximum; true where some lane's reference moves, to next
+  template <int kEarly>
+  __device__ static inline bool restarts(int n) { return n < 64 ? n % kEarly == 0 : n % 4 == 0; }
+  // Takes a tile's maximum; true where some lane's reference moves, to next
   // (what it was is left in ref for the rescale, and set by the caller).
-  __device__ inline bool take(float mt, int n, float& next) {
+  __device__ inline bool take(float mt, bool restart, float& next) {
     most = fmaxf(most, mt);
-    if (restarts(n)) {  // uniform
+    if (restart) {  // uniform
       const float w = fmaxf(mt, most - 100.0f);  // (finite after a finite tile)
       next = w + fmaxf(0.0f, ceilf(most - w));
     } else {
@@ -387,7 +390,7 @@ __global__ __launch_bounds__(kWave* NG) void hyb_sp_partial_kernel(
     float mn;
     bool moves;
     if constexpr (kWin) {
-      moves = rf.take(mt, n, mn);
+      moves = rf.take(mt, SpRef::restarts<2>(n), mn);
     } else {
       mn = fmaxf(m, mt);
       moves = __any(mn > m);
@@ -486,6 +489,10 @@ struct SpRing {
   __device__ static constexpr int vswz(int t) { return 4 * ((t / RP256) % (CPR / 4)); }
 };
 
+// c ? a : b of values: written out over two captured variables it is a choice of
+// their addresses, which can leave a lambda's captures in scratch memory.
+__device__ inline const bf16* sp_pick(bool c, const bf16* a, const bf16* b) { return c ? a : b; }
+
 template <int D>
 struct alignas(16) SpSlot {
   bf16 k[kTile * D];
@@ -493,7 +500,7 @@ struct alignas(16) SpSlot {
 };
 
 template <int D, int NG, bool PAGED>
-__global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefixArgs a, int fill,
+__global__ __launch_bounds__(kWave* NG, D == 64 && NG == 8 ? 4 : 2) void hyb_sp_ring_kernel(SoftmaxPrefixArgs a, int fill,
                                                                     int limit) {
   typedef Mma<bf16> M;
   typedef typename M::op_t op_t;
@@ -561,28 +568,41 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
     voff[u] = (int)(((size_t)t * kstride + (size_t)((pos ^ sw) * EPC)) * sizeof(bf16));
   }
   const int cend = min(hi, P);  // keys below this come from the cache
+  // The order of the tiles.  Those that reach past the cache (the range's last
+  // one or two, nlate of them: a block is at most a tile long) come first, the last
+  // one foremost: their copies are all issued before the loop, and only tile 0
+  // can be partial, so the loop's steps need neither the general copies nor
+  // masks.  (With them last and a second set of steps for the last tiles the
+  // code was twice as long, and a short range, which runs it once, waited for its
+  // instructions: with one head per KV head at d = 128 one request of 300 keys
+  // took 21.4 us, now 15.7, 32 of 512 28.1 and 24.1, 32 of 4096 138 and 115.)
+  const int nlate = ntiles - (cend > lo ? (cend - lo) / kTile : 0);
+  auto first_key = [&](int n) __attribute__((always_inline)) {
+    return lo + (n < nlate ? ntiles - 1 - n : n - nlate) * kTile;
+  };
   constexpr int NKV = NG == 1 ? 2 : 1;      // kinds of copies per wave
   constexpr int IPK = IPW / NKV;            // copies per kind
-  // This wave's copies u0 .. u0 + IPK - 1, of kind kv, of tile n into dst
-  // (keys past the range read the range's last key, in bounds, and are
-  // masked below).
-  auto issue_kind = [&](int kv, int u0, int n, bf16* dst) __attribute__((always_inline)) {
-    const int j0 = lo + n * kTile;
-    const bf16* cb = kv == 0 ? kc : vc;
-    if (j0 + kTile <= cend) {
-      if constexpr (PAGED) {
-        const int pi = j0 >> a.page_shift;
-        cb += ((ptrdiff_t)__builtin_amdgcn_readfirstlane(pages[pi - p0]) - pi) *
-              ((ptrdiff_t)kstride << a.page_shift);
-      }
-      cb += (size_t)j0 * kstride;
-      const int span = (int)((size_t)kTile * kstride * sizeof(bf16));
-      const __amdgpu_buffer_rsrc_t rs =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(cb), 0, span, kBufferWord3);
-#pragma unroll
-      for (int u = u0; u < u0 + IPK; ++u) buf_to_lds16(rs, dst + (w * IPW + u) % IK * RPI * D, voff[u], 0);
-      return;
+  // This wave's copies u0 .. u0 + IPK - 1, of kind kv, of tile n into dst.
+  auto issue_cached = [&](int kv, int u0, int n, bf16* dst) __attribute__((always_inline)) {
+    const int j0 = lo + (n - nlate) * kTile;
+    const bf16* cb = sp_pick(kv == 0, kc, vc);
+    if constexpr (PAGED) {
+      const int pi = j0 >> a.page_shift;
+      cb += ((ptrdiff_t)__builtin_amdgcn_readfirstlane(pages[pi - p0]) - pi) *
+            ((ptrdiff_t)kstride << a.page_shift);
     }
+    cb += (size_t)j0 * kstride;
+    const int span = (int)((size_t)kTile * kstride * sizeof(bf16));
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(cb), 0, span, kBufferWord3);
+#pragma unroll
+    for (int u = u0; u < u0 + IPK; ++u) buf_to_lds16(rs, dst + (w * IPW + u) % IK * RPI * D, voff[u], 0);
+  };
+  // The same of a tile that reaches past the cache (keys past the range read
+  // the range's last key, in bounds, and are masked below).
+  auto issue_general = [&](int kv, int u0, int n, bf16* dst) __attribute__((always_inline)) {
+    const int j0 = first_key(n);
+    const bf16* cb = sp_pick(kv == 0, kc, vc);
     if constexpr (PAGED) {
       // the tile's rows (clamped to the range, all >= j0) lie in the page of
       // row j0: that page's base, shifted so that base + j * kstride is row j
@@ -591,26 +611,36 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
         cb += ((ptrdiff_t)pages[pi - p0] - pi) * ((ptrdiff_t)kstride << a.page_shift);
       }
     }
-    const bf16* blk = kv == 0 ? kbk : vbk;
+    const bf16* blk = sp_pick(kv == 0, kbk, vbk);
 #pragma unroll
     for (int u = u0; u < u0 + IPK; ++u) {
       const int i = (w * IPW + u) % IK;
       const int t = i * RPI + lane / CPR, pos = lane % CPR;
       const int j = min(j0 + t, hi - 1);
-      const bf16* row = j < P ? cb + (size_t)j * kstride : blk + (size_t)(j - P) * kstride;
+      const bf16* row = sp_pick(j < P, cb, blk) + (size_t)(j < P ? j : j - P) * kstride;
       __builtin_amdgcn_global_load_lds(
           (const __attribute__((address_space(1))) void*)(row + (pos ^ (kv == 0 ? RG::swz(t) : RG::vswz(t))) * EPC),
           (__attribute__((address_space(3))) void*)(dst + i * RPI * D), 16, 0, 0);
     }
   };
-  // The copies of step n: K of tile nk and V of tile nv, where they exist.
-  auto issue = [&](int nk, SpSlot<D>& sk, int nv, SpSlot<D>& sv) __attribute__((always_inline)) {
+  // The copies of step n: K of tile nk and V of tile nv, where they exist
+  // (early: tiles 0 and 1, which may reach past the cache).
+  auto issue = [&](auto early, int nk, SpSlot<D>& sk, int nv, SpSlot<D>& sv) __attribute__((always_inline)) {
+    auto one = [&](int kv, int u0, int n, bf16* dst) __attribute__((always_inline)) {
+      if constexpr (decltype(early)::value) {
+        if (n < nlate) {
+          issue_general(kv, u0, n, dst);
+          return;
+        }
+      }
+      issue_cached(kv, u0, n, dst);
+    };
     if constexpr (NG == 1) {
-      if (nk < ntiles) issue_kind(0, 0, nk, sk.k);
-      if (nv >= 0 && nv < ntiles) issue_kind(1, IPK, nv, sv.v);
+      if (nk < ntiles) one(0, 0, nk, sk.k);
+      if (nv >= 0 && nv < ntiles) one(1, IPK, nv, sv.v);
     } else {
       const int kv = w * IPW / IK, n = kv == 0 ? nk : nv;
-      if (n >= 0 && n < ntiles) issue_kind(kv, 0, n, kv == 0 ? sk.k : sv.v);
+      if (n >= 0 && n < ntiles) one(kv, 0, n, kv == 0 ? sk.k : sv.v);
     }
   };
 
@@ -645,12 +675,12 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
   f32x16 sc;
   // Takes the scores of tile n into sc and the reference.  The accumulators are
   // rescaled only when some query's reference moved: once the maximum settles
-  // most tiles skip the 64 multiplies.  Keys past the range, in the range's
-  // last tile only, are masked.
+  // most tiles skip the 64 multiplies.  Keys past the range, in tile 0 only,
+  // are masked.
   auto take_scores = [&](auto check, int n, const f32x16& s) __attribute__((always_inline)) {
     sc = s;
     if constexpr (decltype(check)::value) {
-      const int j0 = lo + n * kTile;
+      const int j0 = first_key(n);
       if (j0 + kTile > hi) {  // uniform
 #pragma unroll
         for (int i = 0; i < 16; ++i) sc[i] = j0 + row_of(i, hh) < hi ? sc[i] : -INFINITY;
@@ -661,7 +691,7 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
     for (int i = 1; i < 16; ++i) mt = fmaxf(mt, sc[i]);
     mt = fmaxf(mt, xor32(mt));
     float mn;
-    if (rf.take(mt * scale, n, mn)) {
+    if (rf.take(mt * scale, SpRef::restarts<1>(n), mn)) {
       const float corr = __builtin_amdgcn_exp2f(m - mn);
       lsum[0] *= corr;
 #pragma unroll
@@ -674,7 +704,7 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
 
   // Weights and P V of tile n (its scores in sc, its V in vt) and the scores
   // of tile n + 1 (its K in kt; not with LAST), then that tile's maximum.
-  auto compute = [&](auto last, auto check, int n, const bf16* kt, const bf16* vt) __attribute__((always_inline)) {
+  auto compute = [&](auto last, int n, const bf16* kt, const bf16* vt) __attribute__((always_inline)) {
     constexpr bool LAST = decltype(last)::value;
     op_t kop[KD];
     if constexpr (!LAST) {
@@ -735,7 +765,7 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
         __builtin_amdgcn_sched_group_barrier(0x100, 4 * NCT * KL / KD, 0);
         __builtin_amdgcn_sched_group_barrier(0x402, 6, 0);
       }
-      take_scores(check, n + 1, sn);
+      take_scores(std::false_type{}, n + 1, sn);
     }
   };
 
@@ -757,26 +787,25 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
   // With one wave, a step's copies are K n + 1 and V n; whole steps are
   // counted while both kinds are still issued.
   const int ahead = NG == 1 || w * IPW / IK == 0 ? 1 : 0;
-  auto step = [&](int n, auto S, auto check) __attribute__((always_inline)) {
+  auto step = [&](int n, auto S) __attribute__((always_inline)) {
     constexpr int SV = decltype(S)::value;
     const int later = ntiles - 1 - n - ahead;
     if constexpr (NG == 1) wait_step(later >= 2 ? 2 : 0);
     else wait_step(min(2, later));
     lds_barrier_nodrain();  // K n+1 and V n visible everywhere; K n's and V n-1's slots free
-    issue(n + R, slot(S), n + R - 1, slot(std::integral_constant<int, (SV + R - 1) % R>{}));
-    compute(std::false_type{}, check, n, slot(std::integral_constant<int, (SV + 1) % R>{}).k, slot(S).v);
+    issue(std::false_type{}, n + R, slot(S), n + R - 1, slot(std::integral_constant<int, (SV + R - 1) % R>{}));
+    compute(std::false_type{}, n, slot(std::integral_constant<int, (SV + 1) % R>{}).k, slot(S).v);
   };
 
   // Copies of K 0 .. R-1 and V 0 .. R-2, in the order of the steps' copies.
-  issue(0, s0, -1, s0);
-  issue(1, s1, 0, s0);
-  issue(2, s2, 1, s1);
-  issue(3, s3, 2, s2);
+  const std::true_type yes{};
+  issue(yes, 0, s0, -1, s0);
+  issue(yes, 1, s1, 0, s0);
+  issue(yes, 2, s2, 1, s1);  // (K of tile 2 is a cached tile's)
+  issue(std::false_type{}, 3, s3, 2, s2);
   if constexpr (NG == 1) wait_step(ntiles >= R ? 3 : 0);
   else wait_step(ahead ? min(3, ntiles - 1) : 3);  // (V's waves need nothing yet)
   lds_barrier_nodrain();
-  const std::false_type no{};
-  const std::true_type yes{};
   {
     f32x16 s = {};
 #pragma unroll
@@ -784,21 +813,20 @@ __global__ __launch_bounds__(kWave* NG, 2) void hyb_sp_ring_kernel(SoftmaxPrefix
     take_scores(yes, 0, s);
   }
   int n = 0;
-  for (; n + R + 1 < ntiles; n += R) {
-    step(n, std::integral_constant<int, 0>{}, no);
-    step(n + 1, std::integral_constant<int, 1>{}, no);
-    step(n + 2, std::integral_constant<int, 2>{}, no);
-    step(n + 3, std::integral_constant<int, 3>{}, no);
+  for (; n + R < ntiles; n += R) {
+    step(n, std::integral_constant<int, 0>{});
+    step(n + 1, std::integral_constant<int, 1>{});
+    step(n + 2, std::integral_constant<int, 2>{});
+    step(n + 3, std::integral_constant<int, 3>{});
   }
-  const int rest = ntiles - n;  // 1 .. R + 1
-  if (rest > 1) step(n, std::integral_constant<int, 0>{}, yes);
-  if (rest > 2) step(n + 1, std::integral_constant<int, 1>{}, yes);
-  if (rest > 3) step(n + 2, std::integral_constant<int, 2>{}, yes);
-  if (rest > 4) step(n + 3, std::integral_constant<int, 3>{}, yes);
+  if (n + 1 < ntiles) step(n, std::integral_constant<int, 0>{});
+  if (n + 2 < ntiles) step(n + 1, std::integral_constant<int, 1>{});
+  if (n + 3 < ntiles) step(n + 2, std::integral_constant<int, 2>{});
   // the last tile: every copy has landed
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   lds_barrier_nodrain();
-  compute(yes, yes, ntiles - 1, nullptr, rest == 2 ? s1.v : rest == 3 ? s2.v : rest == 4 ? s3.v : s0.v);
+  const int rest = ntiles - n;  // 1 .. R
+  compute(yes, ntiles - 1, nullptr, rest == 2 ? s1.v : rest == 3 ? s2.v : rest == 4 ? s3.v : s0.v);
 
   if (li >= L) return;
   const float l = lsum[0];
