@@ -49,7 +49,10 @@ struct SpCfg {
 };
 
 constexpr int kMaxGroup = 8;  // query heads per KV head handled by one WG
-constexpr int kMaxRange = 65536;  // keys of one split range at most
+// Keys of one split range at most: 32768 cached keys and a block fit one, and
+// the page numbers of so many leave room for four of the paged ring's
+// workgroups on a CU at d = 64 (65536 would leave room for three).
+constexpr int kMaxRange = 49152;
 // pages of one range at the smallest page size (32), unaligned ends included
 constexpr int kMaxRangePages = kMaxRange / 32 + 2;
 
@@ -72,73 +75,139 @@ __device__ inline int sp_tiles(const SoftmaxPrefixArgs& a, int b) {
 // How the requests' keys are cut.  The lengths are known on the device only,
 // so every workgroup works the cut out for itself, from prefix_len alone and
 // with the same result: request b gets ceil(tiles_b / c) ranges, numbered
-// through over the requests (its first is number base_b), and range s of
-// request b takes an even share of its tiles.  The tiles per range c is the
-// candidate with the least estimated time, rounds * (c + the cost of a
-// range): rounds of `fill` ranges (the workgroups the chip holds at once, per
-// KV head), and a range costs its start, its partial result and that result's
-// merge, about kRangeCost tiles.  Candidates lie around the even share of the
-// chip; the last one cuts the longest request into limit / B ranges, so that
-// all ranges fit the grid and the workspace.
+// through over the requests (so that the workgroups that have a range come first
+// and spread over the chip; a fixed number of places per request took 8 paged
+// requests of 1 to 4096 keys from 29 to 34 us), and range s of request b takes
+// an even share of its tiles.  The tiles per range c is the
+// candidate with the least estimated time (in whole numbers, so that every kernel
+// finds the same).  Per KV head, `sat` workgroups use the memory fully and the
+// chip holds `slots` of them at once.  Up to `sat` ranges take the time of the
+// longest.  More, as far as they all fit, share the memory: the time of all their
+// tiles (a tenth more, as they don't end together), or of the longest among as
+// many neighbours as its CU has, half of whom end early, if that is more.  Ranges
+// beyond that also pay for the part of the last round that stays empty.  A range
+// costs its start, its partial result and that result's merge besides its tiles
+// (sp_range_cost).  Candidates lie around the even share of `sat`; the
+// last one cuts the longest request into limit / B ranges, so that all ranges fit
+// the grid and the workspace.
 // Equal cuts of max_prefix into n_split ranges, as it was, make 2048
 // workgroups whatever the lengths: four rounds and a merge where one round of
 // whole requests fills the chip (128 requests of 32768 keys: 1.70 against
 // 1.54 ms, the loop below included), and ranges past a short request's end
 // that still write, and have merged, an empty result (24 requests of 1 to
-// 8192 keys: 104 against 76 us; 8 of 32768: 232 against 137 us).  A round and
-// a half (fill for three or four workgroups per CU) is slower: 1.63 ms,
-// 114 us, 220 us.
-struct SpPlan {
-  int c;      // tiles per range, before the even share
-  bool whole; // every request is one range
+// 8192 keys: 104 against 76 us; 8 of 32768: 232 against 137 us).
+struct SpCut {
+  int slots, sat, limit;
+  int layer;  // ranges per KV head that give every CU one workgroup
+  int c;      // tiles per range where the host cuts, else 0
 };
-constexpr int kRangeCost = 10;
-constexpr int kCand = 16;        // candidates; kWave / kCand lanes share one
+struct SpPlan {
+  int c;       // tiles per range, before the even share
+  bool whole;  // every request is one range
+};
+constexpr int kCand = 16;        // candidates; kWave / kCand = 4 lanes share one
 constexpr int kPlanTiles = 256;  // requests staged in LDS at most
 
-// tiles: LDS scratch of kPlanTiles + 2 ints.  All threads of the workgroup;
-// the first wave plans.
-__device__ inline SpPlan sp_plan(const SoftmaxPrefixArgs& a, int fill, int limit, int* tiles) {
+// A range's cost in tiles: its start (a tile of d = 64 is half as long) and the
+// fp32 rows of its G heads and L queries, written and read once; at most ten.
+__device__ inline int sp_range_cost(const SoftmaxPrefixArgs& a) {
+  return min(10, (a.s.D == 128 ? 2 : 4) + a.s.Hq / a.s.Hkv * a.s.L / (a.s.dtype == 1 ? 16 : 32));
+}
+
+// Sum or maximum over the wave, in every lane: rotations within the rows of 16
+// lanes, then exchanges of rows.  (Six shuffles through LDS took 0.3 us, and a
+// plan and its use are several of these.)
+template <typename Op>
+__device__ inline int wave_all(int x, Op op) {
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, false));  // row_ror:8
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x124, 0xf, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x122, 0xf, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x121, 0xf, 0xf, false));
+  auto f = [](int v) { return __builtin_bit_cast(float, v); };
+  x = op(x, __builtin_bit_cast(int, xor16(f(x))));
+  return op(x, __builtin_bit_cast(int, xor32(f(x))));
+}
+struct AddOp {
+  __device__ int operator()(int a, int b) const { return a + b; }
+};
+struct MaxOp {
+  __device__ int operator()(int a, int b) const { return max(a, b); }
+};
+struct MinOp {
+  __device__ int operator()(int a, int b) const { return min(a, b); }
+};
+// Sum over the lanes up to this one.
+__device__ inline int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
+  return x;
+}
+
+// tiles: LDS scratch of kPlanInts ints.  All threads of the workgroup; the
+// first wave plans.  (The scratch is part of a tile buffer that is first written
+// behind a later barrier: on its own it would cost d = 64 one of five workgroups
+// on a CU.)
+constexpr int kPlanInts = kPlanTiles + 2;
+__device__ inline SpPlan sp_plan(const SoftmaxPrefixArgs& a, const SpCut& cut, int* tiles) {
   const int B = a.s.B, tid = threadIdx.x;
   if (a.n_split == 1) return SpPlan{1 << 24, true};
-  if (fill < 0) return SpPlan{-fill, false};  // cut by the host
+  if (cut.c > 0) return SpPlan{cut.c, false};
   if (tid < kWave) {
     int total = 0, most = 0;
-    for (int b0 = tid; b0 < B; b0 += kWave) {
-      const int nt = sp_tiles(a, b0);
+    const int end = B <= kPlanTiles ? (B + 15) & ~15 : B;  // (padded with empty requests)
+    for (int b0 = tid; b0 < end; b0 += kWave) {
+      const int nt = b0 < B ? sp_tiles(a, b0) : 0;
       if (B <= kPlanTiles) tiles[b0] = nt;
       total += nt;
       most = max(most, nt);
     }
-    for (int x = 1; x < kWave; x <<= 1) {
-      total += __shfl_xor(total, x);
-      most = max(most, __shfl_xor(most, x));
-    }
-    __builtin_amdgcn_wave_barrier();  // (tiles: written and read by this wave)
-    const int share = max(1, (total + fill - 1) / fill);
+    total = __builtin_amdgcn_readfirstlane(wave_all(total, AddOp{}));
+    most = __builtin_amdgcn_readfirstlane(wave_all(most, MaxOp{}));
+    // (tiles: written and read by this wave)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    const int share = max(1, (total + cut.sat - 1) / cut.sat);
     const int cand = tid % kCand, sub = tid / kCand;
     // 1/4, 1/3, 1/2, 3/4, then from 1 on in steps of 1/16 to 1 1/2, 2, 4
     const int num = cand < 4 ? (cand == 0 ? 12 : cand == 1 ? 16 : cand == 2 ? 24 : 36)
                     : cand < 13 ? 48 + 3 * (cand - 4) : cand == 13 ? 96 : 192;
     int c = (int)(((long)share * num + 47) / 48);
     c = min(max(c, 4), kMaxRange / kTile);
-    const int least = max(1, limit / B);
+    const int least = max(1, cut.limit / B);
     if (cand == kCand - 1) c = (most + least - 1) / least;
+    // the candidate's ranges: x / c by a reciprocal, within one of it, so that
+    // the correction leaves one too many at worst and never too few (c times the
+    // quotient's error is below one for x up to 5 million); exact beyond
     const float rc = 1.0f / (float)c;
+    auto ranges = [&](int x) {
+      if (x >= 1 << 20) return (x + c - 1) / c;
+      const int n = (int)((float)x * rc);
+      return n + (n * c < x ? 1 : 0);
+    };
     int sum = 0;
-    for (int b0 = sub; b0 < B; b0 += kWave / kCand) {
-      const int x = B <= kPlanTiles ? tiles[b0] : sp_tiles(a, b0);
-      const int n = (int)((float)x * rc);  // x / c, within one
-      sum += n + (n * c < x ? 1 : 0);      // one too many at worst, never too few
+    if (B <= kPlanTiles) {
+      for (int b0 = 4 * sub; b0 < end; b0 += 16) {
+        const int4 x = *reinterpret_cast<const int4*>(tiles + b0);
+        sum += ranges(x.x) + ranges(x.y) + ranges(x.z) + ranges(x.w);
+      }
+    } else {
+      for (int b0 = sub; b0 < B; b0 += kWave / kCand) sum += ranges(sp_tiles(a, b0));
     }
-    for (int x = kCand; x < kWave; x <<= 1) sum += __shfl_xor(sum, x);
-    const int rounds = (sum + fill - 1) / fill;
-    const float cost = sum <= limit || cand == kCand - 1
-                           ? (float)rounds * (float)(min(c, most) + (sum > B ? kRangeCost : 0))
-                           : INFINITY;
-    float best = cost;
-    for (int x = 1; x < kWave; x <<= 1) best = fminf(best, __shfl_xor(best, x));
-    const int at = __builtin_ctzll(__ballot(cost == best));
+    static_assert(kCand == 16, "the lanes that share a candidate are a row apart");
+    sum += __builtin_bit_cast(int, xor16(__builtin_bit_cast(float, sum)));
+    sum += __builtin_bit_cast(int, xor32(__builtin_bit_cast(float, sum)));
+    const int extra = sum > B ? sp_range_cost(a) : 0, longest = min(c, most) + extra;
+    const int work = (min(total, 1 << 26) + sum * extra) * 11 / 10, rest = sum % cut.slots;
+    int time = longest * cut.sat;
+    if (sum > cut.slots)
+      time = work + (rest > 0 ? time * (cut.slots - rest) / cut.slots : 0);
+    else if (sum > cut.sat)
+      time = max(longest * (cut.sat + (sum + cut.layer - 1) / cut.layer * cut.layer) / 2, work);
+    const int cost = sum <= cut.limit ? time : cand == kCand - 1 ? 0x7ffffffe : 0x7fffffff;
+    const int at = __builtin_ctzll(__ballot(cost == wave_all(cost, MinOp{})));
     const int pick = __builtin_amdgcn_readlane(c, at);
     if (tid == 0) {
       tiles[kPlanTiles] = pick;
@@ -158,40 +227,34 @@ __device__ inline int sp_ranges(const SpPlan& p, int nt) { return (nt + p.c - 1)
 // request is one range, that is request r; else the ranges of the requests
 // before are summed, 64 requests at a time.  (Summed in every case, calls of
 // many short requests paid for it: 4096 requests of 64 keys 907 us, now 377;
-// 4096 of 32 at 8 KV heads of d = 64 584 us, now 145.)
+// 4096 of 32 at 8 KV heads of d = 64 584 us, now 141.)
 struct SpRange {
   int b, s, n, lo, hi;
 };
+__device__ inline SpRange sp_share(const SoftmaxPrefixArgs& a, int b, int s, int n) {
+  // an even share of the tiles: the first tiles % n ranges take one more
+  const int keys = sp_keys(a, b), tiles = (keys + kTile - 1) / kTile;
+  const int each = tiles / n, more = tiles % n;
+  const int t0 = s * each + min(s, more);
+  return SpRange{b, s, n, t0 * kTile, min((t0 + each + (s < more ? 1 : 0)) * kTile, keys)};
+}
 __device__ inline SpRange sp_range(const SoftmaxPrefixArgs& a, const SpPlan& p, int r, int lane) {
   const int B = a.s.B;
-  if (p.whole) return r < B ? SpRange{r, 0, 1, 0, sp_keys(a, r)} : SpRange{-1, 0, 0, 0, 0};
+  const SpRange none{-1, 0, 0, 0, 0};
+  if (p.whole) return r < B ? SpRange{r, 0, 1, 0, sp_keys(a, r)} : none;
   int base = 0;
   for (int b0 = 0; b0 < B; b0 += kWave) {
-    const int nt = b0 + lane < B ? sp_tiles(a, b0 + lane) : 0;
-    const int n = b0 + lane < B ? sp_ranges(p, nt) : 0;
-    int end = n;  // inclusive sum over the lanes
-    for (int x = 1; x < kWave; x <<= 1) {
-      const int y = __shfl_up(end, x);
-      if (lane >= x) end += y;
-    }
+    const int n = b0 + lane < B ? sp_ranges(p, sp_tiles(a, b0 + lane)) : 0;
+    const int end = wave_scan(n);
     const int all = __builtin_amdgcn_readlane(end, kWave - 1);
     if (r < base + all) {
       const int at = __builtin_ctzll(__ballot(r < base + end));
-      SpRange q;
-      q.b = b0 + at;
-      q.n = __builtin_amdgcn_readlane(n, at);
-      q.s = r - base - (__builtin_amdgcn_readlane(end, at) - q.n);
-      const int tiles = __builtin_amdgcn_readlane(nt, at);
-      // an even share of the tiles: the first tiles % n ranges take one more
-      const int each = tiles / q.n, more = tiles % q.n;
-      const int t0 = q.s * each + min(q.s, more);
-      q.lo = t0 * kTile;
-      q.hi = min((t0 + each + (q.s < more ? 1 : 0)) * kTile, sp_keys(a, q.b));
-      return q;
+      const int nb = __builtin_amdgcn_readlane(n, at);
+      return sp_share(a, b0 + at, r - base - (__builtin_amdgcn_readlane(end, at) - nb), nb);
     }
     base += all;
   }
-  return SpRange{-1, 0, 0, 0, 0};
+  return none;
 }
 
 // Partial results in the workspace, by range number r: rows of D floats
@@ -249,7 +312,7 @@ struct SpRef {
 // the end of the step, so one barrier per tile orders everything.
 template <typename T, int D, int NG, bool PAGED>
 __global__ __launch_bounds__(kWave* NG) void hyb_sp_partial_kernel(
-    SoftmaxPrefixArgs a, int fill, int limit) {
+    SoftmaxPrefixArgs a, SpCut cut) {
   typedef SpCfg<T, D, NG> C;
   typedef typename C::M M;
   typedef typename C::op_t op_t;
@@ -262,8 +325,8 @@ __global__ __launch_bounds__(kWave* NG) void hyb_sp_partial_kernel(
   const int Hq = a.s.Hq, Hkv = a.s.Hkv, L = a.s.L, G = Hq / Hkv;
   const int Pmax = a.max_prefix;
   const int g = blockIdx.x % Hkv, r = blockIdx.x / Hkv, h = g * G + w;
-  __shared__ int plan[kPlanTiles + 2];
-  const SpRange rg = sp_range(a, sp_plan(a, fill, limit, plan), r, lane);
+  static_assert(sizeof(sh.v[1]) >= kPlanInts * sizeof(int), "the plan's scratch fits a tile");
+  const SpRange rg = sp_range(a, sp_plan(a, cut, reinterpret_cast<int*>(sh.v[1])), r, lane);
   if (rg.b < 0) return;  // uniform: past the plan's last range
   const int b = rg.b, lo = rg.lo, hi = rg.hi;
   const int P = sp_keys(a, b) - L;
@@ -500,8 +563,7 @@ struct alignas(16) SpSlot {
 };
 
 template <int D, int NG, bool PAGED>
-__global__ __launch_bounds__(kWave* NG, D == 64 && NG == 8 ? 4 : 2) void hyb_sp_ring_kernel(SoftmaxPrefixArgs a, int fill,
-                                                                    int limit) {
+__global__ __launch_bounds__(kWave* NG, D == 64 && NG == 8 ? 4 : 2) void hyb_sp_ring_kernel(SoftmaxPrefixArgs a, SpCut cut) {
   typedef Mma<bf16> M;
   typedef typename M::op_t op_t;
   typedef SpRing<D> RG;
@@ -521,8 +583,8 @@ __global__ __launch_bounds__(kWave* NG, D == 64 && NG == 8 ? 4 : 2) void hyb_sp_
   // token rows of the cache (each its 1/Hkv share of every row) start
   // together.
   const int g = blockIdx.x % Hkv, r = blockIdx.x / Hkv, h = g * G + w;
-  __shared__ int plan[kPlanTiles + 2];
-  const SpRange rg = sp_range(a, sp_plan(a, fill, limit, plan), r, lane);
+  static_assert(sizeof(s3.v) >= kPlanInts * sizeof(int), "the plan's scratch fits a tile");
+  const SpRange rg = sp_range(a, sp_plan(a, cut, reinterpret_cast<int*>(s3.v)), r, lane);
   if (rg.b < 0) return;  // uniform: past the plan's last range
   const int b = rg.b, lo = rg.lo, hi = rg.hi;
   const int P = sp_keys(a, b) - L;
@@ -869,11 +931,11 @@ __global__ __launch_bounds__(kWave* NG, D == 64 && NG == 8 ? 4 : 2) void hyb_sp_
 // the rows requested after the maxima took 13.7 us (8 requests: 7.2, now
 // 5.4).
 template <typename T, int D>
-__global__ __launch_bounds__(256) void hyb_sp_combine_kernel(SoftmaxPrefixArgs a, int fill, int limit) {
+__global__ __launch_bounds__(256) void hyb_sp_combine_kernel(SoftmaxPrefixArgs a, SpCut cut) {
   constexpr int TPR = D / 4;              // threads per row
   constexpr int RPB = 256 / TPR;          // rows per unit
-  __shared__ int plan[kPlanTiles + 2];
-  const SpPlan p = sp_plan(a, fill, limit, plan);
+  __shared__ alignas(16) int plan[kPlanInts];
+  const SpPlan p = sp_plan(a, cut, plan);
   if (p.whole) return;  // every row is already written out
   const int Hq = a.s.Hq, L = a.s.L, lane = threadIdx.x & (kWave - 1);
   const int upb = (L + RPB - 1) / RPB;    // units of a (request, head)
@@ -886,7 +948,7 @@ __global__ __launch_bounds__(256) void hyb_sp_combine_kernel(SoftmaxPrefixArgs a
     if (n == 1) continue;  // uniform: already written out
     int base = 0;
     for (int b0 = lane; b0 < b; b0 += kWave) base += sp_ranges(p, sp_tiles(a, b0));
-    for (int x = 1; x < kWave; x <<= 1) base += __shfl_xor(base, x);
+    base = wave_all(base, AddOp{});
     const int i = u % upb * RPB + threadIdx.x / TPR, c = (threadIdx.x % TPR) * 4;
     if (i >= L) continue;  // (no barrier or exchange follows in this unit)
     const size_t row0 = sp_row(a, base, h, i);
@@ -954,18 +1016,36 @@ size_t softmax_prefix_ws_bytes(const Shape& s, int n_split) {
   return (size_t)s.B * s.Hq * n_split * s.L * (s.D + 2) * sizeof(float);
 }
 
-template <typename T, int D, bool PAGED>
-static hipError_t sp_go(const SoftmaxPrefixArgs& a, hipStream_t st) {
+// Workgroups of a range kernel that the chip holds at once, by its LDS and
+// registers as built.  Waves go to the four SIMDs in turn: 3, 5, 6 and 7 of them
+// are counted as the next multiple of four (the odd ones seldom fit in between).
+template <typename K>
+static int sp_resident(K kernel, int waves) {
+  int n = 0;
+  const int w = waves <= 2 ? waves : (waves + 3) / 4 * 4;
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, kWave * w, 0);
+  return 256 * (e == hipSuccess ? max(1, n) : 1);
+}
+
+template <typename K>
+static hipError_t sp_launch(K kernel, int resident, int waves, bool ring, const SoftmaxPrefixArgs& a, hipStream_t st,
+                            SpCut* out) {
   const int ns = a.n_split;
-  const int G = a.s.Hq / a.s.Hkv;
-  // Ranges the chip holds at once, per KV head: two workgroups per CU by
-  // their LDS, one with more than 4 waves, by their registers.
-  int fill = max(1, (G > 4 ? 256 : 512) / a.s.Hkv);
+  SpCut cut;
+  // Of the ring's workgroups two per CU, one with more than four waves, keep
+  // the memory as busy as more do, three tiles of each in flight; the
+  // register-staged kernel is bound by its waves' own chains.  (Two, or one, for
+  // every kernel, also as what the chip holds, was right at d = 128 only: at
+  // d = 64 up to five of the ring's workgroups fit: 32 requests of 1024 keys, 8
+  // KV heads of one head, 26.7 us, now 19.2; 32 of 1 to 4096 keys at 16 KV heads,
+  // paged, 115 and 77.)
+  cut.slots = max(1, (waves > 4 ? min(resident, 256) : resident) / a.s.Hkv);
+  cut.sat = ring ? max(1, min(cut.slots, (waves > 4 ? 256 : 512) / a.s.Hkv)) : cut.slots;
   // Ranges of a plan at most: three rounds, within the workspace, and at
   // least what the longest range allows.
   const int need = (int)(((long)a.max_prefix + a.s.L + kMaxRange - 1) / kMaxRange);
-  const int limit = min(a.s.B * ns, max(a.s.B * need, 3 * fill));
-  const dim3 grid(a.s.Hkv * limit);
+  cut.limit = min(a.s.B * ns, max(a.s.B * need, 3 * cut.sat));
+  cut.layer = max(1, 256 / a.s.Hkv);
   // Where ranges of at most 512 keys of full-length requests fit one round,
   // the host cuts every request into those: there is little to gain from the
   // lengths, and working a plan out costs each kernel a few us (32 requests of
@@ -973,42 +1053,58 @@ static hipError_t sp_go(const SoftmaxPrefixArgs& a, hipStream_t st) {
   // 32.7 and 28.8).
   const int tmax = (int)(((long)a.max_prefix + a.s.L + kTile - 1) / kTile);
   const int even = (tmax + ns - 1) / ns;
-  if ((long)a.s.B * ns <= fill && even <= 16) fill = -even;
-  bool launched_ring = false;
-  if constexpr (sizeof(T) == 2) {
-    launched_ring = true;
-    switch (G) {
-      case 1: hipLaunchKernelGGL((hyb_sp_ring_kernel<D, 1, PAGED>), grid, dim3(kWave), 0, st, a, fill, limit); break;
-      case 2: hipLaunchKernelGGL((hyb_sp_ring_kernel<D, 2, PAGED>), grid, dim3(kWave * 2), 0, st, a, fill, limit); break;
-      case 4: hipLaunchKernelGGL((hyb_sp_ring_kernel<D, 4, PAGED>), grid, dim3(kWave * 4), 0, st, a, fill, limit); break;
-      case 8: hipLaunchKernelGGL((hyb_sp_ring_kernel<D, 8, PAGED>), grid, dim3(kWave * 8), 0, st, a, fill, limit); break;
-      default: launched_ring = false;  // the register-staged kernel below
-    }
+  cut.c = 0;
+  if ((long)a.s.B * ns <= cut.slots && even <= 16) {
+    cut.c = even;
+    cut.limit = a.s.B * ns;  // (full-length requests' ranges)
   }
-#define HYB_SP_CASE(NG)                                                               \
-  case NG:                                                                            \
-    hipLaunchKernelGGL((hyb_sp_partial_kernel<T, D, NG, PAGED>), grid, dim3(kWave * NG), 0, st, a, \
-                       fill, limit);                                                        \
-    break;
-  if (!launched_ring) {
-    switch (G) {
-      HYB_SP_CASE(1)
-      HYB_SP_CASE(2)
-      HYB_SP_CASE(3)
-      HYB_SP_CASE(4)
-      HYB_SP_CASE(5)
-      HYB_SP_CASE(6)
-      HYB_SP_CASE(7)
-      HYB_SP_CASE(8)
+  *out = cut;
+  hipLaunchKernelGGL(kernel, dim3(a.s.Hkv * cut.limit), dim3(kWave * waves), 0, st, a, cut);
+  return hipGetLastError();
+}
+
+template <typename T, int D, bool PAGED>
+static hipError_t sp_go(const SoftmaxPrefixArgs& a, hipStream_t st) {
+  SpCut cut;
+  hipError_t e;
+#define HYB_SP_CASE(NG, RING, KERNEL)                                           \
+  case NG: {                                                                    \
+    static const int resident = sp_resident(KERNEL, NG);                        \
+    e = sp_launch(KERNEL, resident, NG, RING, a, st, &cut);                     \
+    break;                                                                      \
+  }
+  // bf16 with 1, 2, 4 or 8 query heads per KV head: the copy ring; else the
+  // register-staged kernel.
+  if constexpr (sizeof(T) == 2) {
+    switch (a.s.Hq / a.s.Hkv) {
+      HYB_SP_CASE(1, true, (hyb_sp_ring_kernel<D, 1, PAGED>))
+      HYB_SP_CASE(2, true, (hyb_sp_ring_kernel<D, 2, PAGED>))
+      HYB_SP_CASE(3, false, (hyb_sp_partial_kernel<T, D, 3, PAGED>))
+      HYB_SP_CASE(4, true, (hyb_sp_ring_kernel<D, 4, PAGED>))
+      HYB_SP_CASE(5, false, (hyb_sp_partial_kernel<T, D, 5, PAGED>))
+      HYB_SP_CASE(6, false, (hyb_sp_partial_kernel<T, D, 6, PAGED>))
+      HYB_SP_CASE(7, false, (hyb_sp_partial_kernel<T, D, 7, PAGED>))
+      HYB_SP_CASE(8, true, (hyb_sp_ring_kernel<D, 8, PAGED>))
+      default: return hipErrorInvalidValue;
+    }
+  } else {
+    switch (a.s.Hq / a.s.Hkv) {
+      HYB_SP_CASE(1, false, (hyb_sp_partial_kernel<T, D, 1, PAGED>))
+      HYB_SP_CASE(2, false, (hyb_sp_partial_kernel<T, D, 2, PAGED>))
+      HYB_SP_CASE(3, false, (hyb_sp_partial_kernel<T, D, 3, PAGED>))
+      HYB_SP_CASE(4, false, (hyb_sp_partial_kernel<T, D, 4, PAGED>))
+      HYB_SP_CASE(5, false, (hyb_sp_partial_kernel<T, D, 5, PAGED>))
+      HYB_SP_CASE(6, false, (hyb_sp_partial_kernel<T, D, 6, PAGED>))
+      HYB_SP_CASE(7, false, (hyb_sp_partial_kernel<T, D, 7, PAGED>))
+      HYB_SP_CASE(8, false, (hyb_sp_partial_kernel<T, D, 8, PAGED>))
       default: return hipErrorInvalidValue;
     }
   }
 #undef HYB_SP_CASE
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || ns == 1) return e;  // one range: already written out
+  if (e != hipSuccess || a.n_split == 1) return e;  // one range: already written out
   const long units = (long)a.s.B * a.s.Hq * ((a.s.L + 1024 / D - 1) / (1024 / D));
   hipLaunchKernelGGL((hyb_sp_combine_kernel<T, D>), dim3((unsigned)std::min<long>(units, 2048)), dim3(256), 0, st,
-                     a, fill, limit);
+                     a, cut);
   return hipGetLastError();
 }
 
