@@ -2403,7 +2403,7 @@ __global__ __launch_bounds__(dv_threads<D>()) void hyb_bwd_dv_kernel(BwdKArgs ka
         for (int i = 0; i < 16; i += 4)
           __builtin_amdgcn_raw_buffer_store_b128(
               __builtin_bit_cast(u32x4, f32x4{ol[i], ol[i + 1], ol[i + 2], ol[i + 3]}), vrs,
-              vlane + 2 * i * (int)sizeof(float), so, 0);
+              (int)((unsigned)vlane + 2 * i * sizeof(float)), so, 0);
       }
       // commit: Gbar += phi(Q)^T dL/dN (this wave's columns)
 #pragma unroll

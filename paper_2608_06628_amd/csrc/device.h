@@ -455,8 +455,9 @@ __device__ inline float log_sigmoid(float a) {
 // format; the untyped loads and stores used here take no other field).
 constexpr int kBufferWord3 = 0x00020000;
 
-// A lane offset past the end of any raw buffer used here (all under 2 GiB):
-// the load returns zero.
+// A lane offset past the end of any raw buffer used here (all under 2 GiB, which
+// the launchers see to): a load returns zero, a store is dropped.  Offsets are
+// added to it unsigned.
 constexpr int kPastBuffer = 0x7ffffff0;
 
 // A 16-byte piece per lane from a buffer straight into LDS: lane l's piece

@@ -1468,9 +1468,12 @@ static hipError_t prefill_delta_go(const PrefillArgs& a, const SegPlan& p, hipSt
   const int units = a.s.B * a.s.Hq;
   if (p.npieces() <= 0) return hipSuccess;
   if constexpr (sizeof(T) == 2 && F <= 64) {
-    hipLaunchKernelGGL((hyb_prefill_delta_pipe_kernel<T, D, F>), dim3(units * p.npieces()),
-                       dim3(delta_pipe_threads<D>()), 0, st, a, p);
-    return hipGetLastError();
+    // (its buffer loads address a request's rows of k and v with 32-bit offsets)
+    if ((size_t)a.T * a.s.Hkv * D * sizeof(T) < ((size_t)1 << 31)) {
+      hipLaunchKernelGGL((hyb_prefill_delta_pipe_kernel<T, D, F>), dim3(units * p.npieces()),
+                         dim3(delta_pipe_threads<D>()), 0, st, a, p);
+      return hipGetLastError();
+    }
   }
   hipLaunchKernelGGL((hyb_prefill_kernel<T, D, F>), dim3(units * p.npieces()),
                      dim3(kWave * (D / kTile)), 0, st, a, p, 1);

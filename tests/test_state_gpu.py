@@ -287,3 +287,29 @@ def test_prefill_blocks_stay_apart(L, d, F):
         assert torch.isfinite(dirty[:, :n]).all()
         assert torch.equal(clean[:, :n], dirty[:, :n])
         assert torch.isnan(dirty[:, n:]).all()
+
+
+def test_prefill_request_past_32_bit_offsets():
+    """A request whose K and V rows take more than 4 GiB each, beyond the 32-bit
+    offsets of the pipelined increments: 1025 copies of one prompt give 1025
+    times its state (up to fp32 sums of 2100 blocks per piece, at most 2100 *
+    2^-24 = 1.3e-4)."""
+    H, d, f, L, T, copies = 8, 128, 128, 32, 2048, 1025
+    announce("prefill of a request past 32-bit offsets")
+    g = torch.Generator(device="cuda").manual_seed(221)
+    rnd = lambda *n, s=1.0: (torch.randn(n, generator=g, device="cuda") * s).to(torch.bfloat16)
+    k, v, W = rnd(1, T, H, d), rnd(1, T, H, d), rnd(H, f // 2, d, s=d ** -0.5)
+    states = []
+    for n in (1, copies):
+        S, z = torch.zeros((1, H, d, f), device="cuda"), torch.zeros((1, H, f), device="cuda")
+        kn, vn = (x.expand(n, T, H, d).reshape(1, n * T, H, d) for x in (k, v))
+        assert n == 1 or kn.numel() * 2 > 1 << 32
+        hb.hybrid_state_prefill(None, kn, vn, W, None, S, z, L, want_out=False)
+        torch.cuda.synchronize()
+        states.append((S.double(), z.double()))
+        del kn, vn
+    torch.cuda.empty_cache()
+    for one, many in zip(*states):
+        err = float((many - copies * one).norm() / many.norm())
+        print(f"[large request] relative error {err:.2e}")
+        assert err <= 1.3e-4
