@@ -424,7 +424,9 @@ __global__ __launch_bounds__(kWave*(D / kTile)) void hyb_prefill_kernel(
 // through a second (written in c+1, read in c+2); z goes from one QS wave to
 // the other through a triple buffer (z_c is written in iteration c and read
 // in c+1).
-// Arithmetic and operand precision are those of the single-group walk above.
+// Operand precision is that of the single-group walk above, except that lin_den
+// takes phi(Q) as the readout does, in bf16; the merge's exponentials, logarithm
+// and reciprocals are the hardware's, about 1 ulp each.
 // A block step is bound by the longest role between two barriers, and by what
 // two waves of a SIMD issue together, so the hand-over costs no instructions
 // that only move bits: phi(K)^T and V^T operands come from row-major tiles by
@@ -580,8 +582,8 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
   lds_barrier();  // z ready
 
   constexpr float kLog2e = 1.4426950408889634f;
-  // logits U^T = W^T X^T of the rows x, from the LDS copy of W_h^T
-  // (W_h^T is held in the feature-map waves' registers, wop)
+  // logits U^T = W^T X^T of the rows x (W_h^T is held in the feature-map waves'
+  // registers, wop)
   auto logits = [&](const op_t (&wop)[NT][C::KD], const op_t (&x)[C::KD], float (&phi)[C::NPAIR][16]) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -788,11 +790,13 @@ __global__ __launch_bounds__(pipe_threads<D>()) void hyb_prefill_pipe_kernel(
         const float m = Bc.m[li], den = Bc.den[li];
         float ca = 1.0f, cz = 0.0f, rz = 0.0f;
         if (lden > 0.0f) {
-          const float la = (lw + m) * kLog2e, lb = __builtin_amdgcn_logf(lden);
+          // (the hardware's logarithm and reciprocal take a subnormal as zero)
+          const float up = lden < 0x1p-100f ? 0x1p64f : 1.0f, x = lden * up;
+          const float la = (lw + m) * kLog2e, lb = __builtin_amdgcn_logf(x) - (up > 1.0f ? 64.0f : 0.0f);
           const float cc = fmaxf(la, lb);
           ca = __builtin_amdgcn_exp2f(la - cc);
           cz = __builtin_amdgcn_exp2f(lb - cc);
-          rz = fast_rcp(lden);
+          rz = fast_rcp(x) * up;
         }
         const float inv = fast_rcp(ca * den + cz);
         if (hh == 0) sh.coef[(c - blk0) & 1][li] = make_float2(ca * inv, cz * rz * inv);

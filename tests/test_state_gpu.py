@@ -313,3 +313,21 @@ def test_prefill_request_past_32_bit_offsets():
         err = float((many - copies * one).norm() / many.norm())
         print(f"[large request] relative error {err:.2e}")
         assert err <= 1.3e-4
+
+
+@pytest.mark.parametrize("e", [-20, -99, -120, -125, -126, -127])
+def test_prefill_tiny_normalisers(e):
+    """The merge of a state whose normaliser phi(q) . z is about 2^e, down into the
+    subnormals, against an in-block branch as small: alpha makes w about 2^e, so
+    that both enter the output (the first block's; S = 0)."""
+    dims = synth.Dims(B=1, Hq=4, Hkv=2, d=64, L=8, F=32, dtype="bf16")
+    announce(f"prefill normaliser 2^{e}")
+    q, k, v = synth.block_qkv(dims, 231, 0.5)
+    Wt, _ = synth.feature_weights(dims, 232, 233)
+    alpha = np.full(4, e * np.log(2.0), np.float32)
+    S = np.zeros((1, 4, 64, 64), np.float32)
+    z = np.full((1, 4, 64), 2.0 ** (e - 1), np.float32)     # phi(q) sums to 2
+    ref, _, _ = oracle.prefill(q, k, v, Wt, alpha, S, z, dims.L)
+    check_outputs(lambda o32: hb.hybrid_state_prefill(
+        act(q, "bf16"), act(k, "bf16"), act(v, "bf16"), act(Wt, "bf16"), f32(alpha), state_dev(S),
+        f32(z), dims.L, out_f32=o32), ref, "bf16", f"prefill normaliser 2^{e}")
