@@ -2628,7 +2628,9 @@ __global__ __launch_bounds__(kWave*(D / kTile), sizeof(T) == 2 ? 2 : 1) void hyb
   HeadRegs hr;
   if constexpr (!kTwo) fetch(0, hr, tid);
 
-  f32x16 dks = {}, dva = {};
+  // On fp32 the score and feature-map parts of dq and dk keep sums of their own
+  // (1/sqrt(d) applied to the whole first one): one chain of both rounds more.
+  f32x16 dks = {}, dkf = {}, dva = {};
   for (int hq = 0; hq < G; ++hq) {
     const int h = g * G + hq;
     const size_t u = (size_t)b * Hq + h;
@@ -2639,7 +2641,7 @@ __global__ __launch_bounds__(kWave*(D / kTile), sizeof(T) == 2 ? 2 : 1) void hyb
     const int lane = tl & (kWave - 1), li = lane & 31, hh = lane >> 5, cc = w * kTile + li;
     const bool lrow = li < L;
     if constexpr (kTwo) fetch(hq, hr, tl);
-    const float lw2 = log_sigmoid(hr.alpha) * kLog2e;
+    const float lw = log_sigmoid(hr.alpha), lw2 = lw * kLog2e;
     lds_barrier();  // the previous head's readers are done
     put(hr, tl);
     if (!kTwo && hq + 1 < G) fetch(hq + 1, hr, tl);  // the next head's operands in flight
@@ -2692,23 +2694,27 @@ __global__ __launch_bounds__(kWave*(D / kTile), sizeof(T) == 2 ? 2 : 1) void hyb
                                               rv, (row_of(r, hh) * D + cc) * (int)sizeof(float), 0, 0));
     }
     __builtin_amdgcn_sched_barrier(0);
-    // w a_ij and dL/ds_ij / sqrt(d) in both orientations (zero outside the
-    // block)
+    // w a_ij and dL/ds_ij (bf16: / sqrt(d)) in both orientations (zero outside
+    // the block)
     f32x16 dsq, ak, dsk;
     {
       const float gdi = sh.gd[li];
+      // (fp32: in base e, without the rounding of the factors log2 e)
+      auto weight = [&](float s) {
+        return E == 1 ? expf(lw + s * scale) : __builtin_amdgcn_exp2f(__builtin_fmaf(s, scale2, lw2));
+      };
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int o = row_of(r, hh);
-        const float aq = (lrow && o < L) ? __builtin_amdgcn_exp2f(__builtin_fmaf(sq[r], scale2, lw2)) : 0.0f;
-        dsq[r] = aq * (pq[r] + gdi) * scale;
-        ak[r] = (lrow && o < L) ? __builtin_amdgcn_exp2f(__builtin_fmaf(sk[r], scale2, lw2)) : 0.0f;
-        dsk[r] = ak[r] * (pk[r] + sh.gd[o]) * scale;
+        const float aq = (lrow && o < L) ? weight(sq[r]) : 0.0f;
+        dsq[r] = aq * (pq[r] + gdi) * (E == 1 ? 1.0f : scale);
+        ak[r] = (lrow && o < L) ? weight(sk[r]) : 0.0f;
+        dsk[r] = ak[r] * (pk[r] + sh.gd[o]) * (E == 1 ? 1.0f : scale);
       }
     }
 
     // dq: sum_j ds_ij k_j + du(q_i) W_h^T
-    f32x16 dqs = {};
+    f32x16 dqs = {}, dqf = {};
 #pragma unroll
     for (int ks = 0; ks < C::KL; ++ks) {
       op_t hi, lo;
@@ -2745,9 +2751,9 @@ __global__ __launch_bounds__(kWave*(D / kTile), sizeof(T) == 2 ? 2 : 1) void hyb
       } else {
         const size_t at = (u * T_ + t0 + min(li, L - 1)) * F + ks * KW + hh * E;
         load_split_op<T>(ka.duq + at, hi, lo);
-        dqs = M::mma(keep_if<T>(lrow, hi), wc, dqs);
+        dqf = M::mma(keep_if<T>(lrow, hi), wc, dqf);
         load_split_op<T>(ka.duk + at, hi, lo);
-        dks = M::mma(keep_if<T>(lrow, hi), wc, dks);
+        dkf = M::mma(keep_if<T>(lrow, hi), wc, dkf);
       }
     }
     // dq of head h: rows i (queries), column cc; rows past L lie past the
@@ -2758,7 +2764,8 @@ __global__ __launch_bounds__(kWave*(D / kTile), sizeof(T) == 2 ? 2 : 1) void hyb
           ((L - 1) * (int)qstride + D) * (int)sizeof(float), kBufferWord3);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float x = dqs[r];  // (bit_cast of a vector's element takes element 0)
+        // (bit_cast of a vector's element takes element 0)
+        const float x = E == 1 ? dqs[r] * scale + dqf[r] : dqs[r];
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), rs,
                                               (row_of(r, hh) * (int)qstride + cc) * (int)sizeof(float), 0, 0);
       }
@@ -2774,7 +2781,7 @@ __global__ __launch_bounds__(kWave*(D / kTile), sizeof(T) == 2 ? 2 : 1) void hyb
   for (int r = 0; r < 16; ++r) {
     const int j = row_of(r, hh);
     if (j < L) {
-      dkd[(size_t)j * kstride] = dks[r];
+      dkd[(size_t)j * kstride] = E == 1 ? dks[r] * scale + dkf[r] : dks[r];
       dvd[(size_t)j * kstride] = dva[r];
     }
   }

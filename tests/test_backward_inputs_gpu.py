@@ -115,3 +115,18 @@ EDGES = [
 @pytest.mark.parametrize("shape", EDGES, ids=lambda s: "x".join(map(str, s)))
 def test_input_gradients_edges(shape):
     test_input_gradients_match_oracle(shape, "dout")
+
+
+def test_input_gradients_fp32_weights():
+    """fp32 weights exp(log w + s) at scores up to about 20: s = q.k / 8 is exact
+    but for its products' sums, so the error of dv is that of the argument's one
+    rounding and the exponential's; with the factors log2 e rounded too it is
+    half as much again (BAD against GOOD)."""
+    announce("backward_full fp32 weights")
+    dims, q, k, v, Wt, alpha, g = _case(2, 128, 8, 4, 64, 32, 32, "f32", seed=151)
+    q, k = q * np.float32(2.5), k * np.float32(2.5)
+    ref = oracle.backward(q, k, v, Wt, alpha, 32, inputs=True, dout=g)
+    got = _run_full(dims, q, k, v, Wt, alpha, 32, dout=g)
+    err = [float(np.linalg.norm(x - r) / np.linalg.norm(r)) for x, r in zip(got[:3], ref[3:])]
+    print("[fp32 weights] dq, dk, dv:", *(f"{e:.3e}" for e in err))
+    assert err[2] <= 6e-7
