@@ -1536,25 +1536,31 @@ SegPlan segment_plan(const Shape& s, int T) {
   return p;
 }
 
-// Workgroups of the walk and of the increments that the chip holds at once:
-// one per CU, by the pipelined kernels' LDS and by the single-group kernel's
-// registers at d = 128 (four waves of one per SIMD); two at d = 64.
+// Workgroups of the walk and of the increments that the plan counts as one
+// round.  One per CU for the pipelined kernels, by their LDS (106 KB of the walk's
+// at d = f = 128; at d = f = 64, 59 and 41 KB, two would fit and are not counted),
+// and for the single-group kernel at d = 128 by its registers (four waves of one
+// per SIMD); two of it at d = 64.
 static int prefill_fill(const Shape& s) {
   return s.dtype == 1 && s.F <= 64 ? 256 : s.D == 64 ? 512 : 256;
 }
 
 // Rounds of n workgroups of the given steps, in steps: workgroups that share a
-// CU slow each other down (a fifth per neighbour).
+// CU slow each other down (a third per neighbour).
 static float prefill_rounds(long n, int fill, float steps) {
   const float share = (float)(n < fill ? n : fill) / 256.0f;
-  return (float)((n + fill - 1) / fill) * steps * (share > 1.0f ? 0.8f + 0.2f * share : 1.0f);
+  return (float)((n + fill - 1) / fill) * steps * (share > 1.0f ? 0.67f + 0.33f * share : 1.0f);
 }
 
 // The prefill's plan: the (segments, pieces per segment) with the least
 // estimated time among those whose pieces fit the workspace of segment_plan.
 // In walk steps: rounds of walk workgroups times a segment's blocks and its
-// start (about 4); rounds of increment workgroups times a piece's blocks, at
-// 0.45 of a step each, and their start (about 2); and the two launches (4).
+// start; rounds of increment workgroups times a piece's blocks, at 0.45 of a step
+// each, and their start; and the two launches.  A start takes about 4 and 2 steps
+// of the pipelined kernels (2 to 3 us each) and the launches 4; of the
+// single-group kernel's steps (10 to 37 us) a start takes 1 or half, the launches
+// half.  (Priced like the pipelined kernels' a prompt of 256 tokens was not cut:
+// fp32 302 us, 205 so; f = 256 127, 96 so.)
 // (Counting two of the fp32 kernel's workgroups per CU at d = 128, where its
 // registers let one in, took 4 x 2048 tokens from 1112 to 1318 us; as counted
 // here they take 1069 us.)
@@ -1564,9 +1570,11 @@ static float prefill_rounds(long n, int fill, float steps) {
 SegPlan prefill_plan(const Shape& s, int T) {
   const int units = s.B * s.Hq, nblk = T / s.L, room = segment_plan(s, T).npieces();
   const int fill = prefill_fill(s);
+  const bool pipe = s.dtype == 1 && s.F <= 64;
+  const float start = pipe ? 4.0f : 1.0f, extra = pipe ? 4.0f : 0.5f;
   SegPlan best;
   best.sb = best.pb = nblk;
-  float least = prefill_rounds(units, fill, (float)(nblk + 4));
+  float least = prefill_rounds(units, fill, (float)nblk + start);
   SegPlan p;
   for (p.nseg = 2; p.nseg <= room + 1 && p.nseg <= nblk; ++p.nseg) {
     p.sb = (nblk + p.nseg - 1) / p.nseg;
@@ -1575,8 +1583,8 @@ SegPlan prefill_plan(const Shape& s, int T) {
       p.pb = (p.sb + p.ppseg - 1) / p.ppseg;
       if ((p.ppseg - 1) * p.pb >= p.sb) continue;  // every piece non-empty
       const long wg = (long)units * p.nseg, dg = (long)units * p.npieces();
-      const float cost = prefill_rounds(wg, fill, (float)(p.sb + 4)) +
-                         prefill_rounds(dg, fill, 0.45f * (float)p.pb + 2.0f) + 4.0f;
+      const float cost = prefill_rounds(wg, fill, (float)p.sb + start) +
+                         prefill_rounds(dg, fill, 0.45f * (float)p.pb + 0.5f * start) + extra;
       if (cost < least) {
         least = cost;
         best = p;
