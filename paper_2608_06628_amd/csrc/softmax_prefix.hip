@@ -1067,36 +1067,39 @@ template <typename T, int D, bool PAGED>
 static hipError_t sp_go(const SoftmaxPrefixArgs& a, hipStream_t st) {
   SpCut cut;
   hipError_t e;
-#define HYB_SP_CASE(NG, RING, KERNEL)                                           \
+  // (a paged cache is cut as the contiguous one is, for the same bits: by what fits
+  // of both their kernels)
+#define HYB_SP_CASE(NG, RING, ...)                                              \
   case NG: {                                                                    \
-    static const int resident = sp_resident(KERNEL, NG);                        \
-    e = sp_launch(KERNEL, resident, NG, RING, a, st, &cut);                     \
+    static const int resident =                                                 \
+        min(sp_resident(__VA_ARGS__, true>, NG), sp_resident(__VA_ARGS__, false>, NG)); \
+    e = sp_launch(__VA_ARGS__, PAGED>, resident, NG, RING, a, st, &cut);        \
     break;                                                                      \
   }
   // bf16 with 1, 2, 4 or 8 query heads per KV head: the copy ring; else the
   // register-staged kernel.
   if constexpr (sizeof(T) == 2) {
     switch (a.s.Hq / a.s.Hkv) {
-      HYB_SP_CASE(1, true, (hyb_sp_ring_kernel<D, 1, PAGED>))
-      HYB_SP_CASE(2, true, (hyb_sp_ring_kernel<D, 2, PAGED>))
-      HYB_SP_CASE(3, false, (hyb_sp_partial_kernel<T, D, 3, PAGED>))
-      HYB_SP_CASE(4, true, (hyb_sp_ring_kernel<D, 4, PAGED>))
-      HYB_SP_CASE(5, false, (hyb_sp_partial_kernel<T, D, 5, PAGED>))
-      HYB_SP_CASE(6, false, (hyb_sp_partial_kernel<T, D, 6, PAGED>))
-      HYB_SP_CASE(7, false, (hyb_sp_partial_kernel<T, D, 7, PAGED>))
-      HYB_SP_CASE(8, true, (hyb_sp_ring_kernel<D, 8, PAGED>))
+      HYB_SP_CASE(1, true, hyb_sp_ring_kernel<D, 1)
+      HYB_SP_CASE(2, true, hyb_sp_ring_kernel<D, 2)
+      HYB_SP_CASE(3, false, hyb_sp_partial_kernel<T, D, 3)
+      HYB_SP_CASE(4, true, hyb_sp_ring_kernel<D, 4)
+      HYB_SP_CASE(5, false, hyb_sp_partial_kernel<T, D, 5)
+      HYB_SP_CASE(6, false, hyb_sp_partial_kernel<T, D, 6)
+      HYB_SP_CASE(7, false, hyb_sp_partial_kernel<T, D, 7)
+      HYB_SP_CASE(8, true, hyb_sp_ring_kernel<D, 8)
       default: return hipErrorInvalidValue;
     }
   } else {
     switch (a.s.Hq / a.s.Hkv) {
-      HYB_SP_CASE(1, false, (hyb_sp_partial_kernel<T, D, 1, PAGED>))
-      HYB_SP_CASE(2, false, (hyb_sp_partial_kernel<T, D, 2, PAGED>))
-      HYB_SP_CASE(3, false, (hyb_sp_partial_kernel<T, D, 3, PAGED>))
-      HYB_SP_CASE(4, false, (hyb_sp_partial_kernel<T, D, 4, PAGED>))
-      HYB_SP_CASE(5, false, (hyb_sp_partial_kernel<T, D, 5, PAGED>))
-      HYB_SP_CASE(6, false, (hyb_sp_partial_kernel<T, D, 6, PAGED>))
-      HYB_SP_CASE(7, false, (hyb_sp_partial_kernel<T, D, 7, PAGED>))
-      HYB_SP_CASE(8, false, (hyb_sp_partial_kernel<T, D, 8, PAGED>))
+      HYB_SP_CASE(1, false, hyb_sp_partial_kernel<T, D, 1)
+      HYB_SP_CASE(2, false, hyb_sp_partial_kernel<T, D, 2)
+      HYB_SP_CASE(3, false, hyb_sp_partial_kernel<T, D, 3)
+      HYB_SP_CASE(4, false, hyb_sp_partial_kernel<T, D, 4)
+      HYB_SP_CASE(5, false, hyb_sp_partial_kernel<T, D, 5)
+      HYB_SP_CASE(6, false, hyb_sp_partial_kernel<T, D, 6)
+      HYB_SP_CASE(7, false, hyb_sp_partial_kernel<T, D, 7)
+      HYB_SP_CASE(8, false, hyb_sp_partial_kernel<T, D, 8)
       default: return hipErrorInvalidValue;
     }
   }

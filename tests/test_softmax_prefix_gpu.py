@@ -60,8 +60,9 @@ def test_no_prefix_equals_hybrid_with_empty_state():
 
 
 RANGES = [
-    # lengths far apart: the plan gives each request its own number of ranges,
-    # of whole tiles; (B, Hq, Hkv, d, L, dtype, Pmax, lengths or a seed)
+    # lengths far apart, in calls small enough that the host cuts every request
+    # into ranges of the same number of whole tiles;
+    # (B, Hq, Hkv, d, L, dtype, Pmax, lengths or a seed)
     (5, 8, 2, 128, 32, "bf16", 6016, [6016, 0, 31, 3000, 4097]),    # 4 heads per KV head
     (3, 2, 2, 64, 9, "bf16", 3008, [3008, 1, 1600]),                # one wave per workgroup
     (3, 4, 2, 128, 1, "bf16", 2080, [65, 2080, 1024]),
@@ -73,14 +74,13 @@ RANGES = [
     # more requests than the plan stages in LDS at once
     (300, 4, 1, 64, 3, "bf16", 1088, 5),
     (2100, 1, 1, 64, 2, "bf16", 544, 6),                            # a range per request at most
-    # more ranges than fit one round, so the plan is made from the lengths
-    # (the smaller calls above are cut alike for every length)
+    # more ranges than fit one round, so the plan is made from the lengths; in
+    # most of these it finds that a range per request is enough (for plans of
+    # several see PLANNED)
     (40, 8, 8, 64, 9, "bf16", 544, 7),
     (40, 32, 8, 128, 32, "bf16", 544, 8),
     (20, 64, 8, 64, 32, "bf16", 544, 9),
-    # fp32: in bf16 the weights' rounding alone, 2^-9 sum(p |v|) / sum(p) and
-    # so up to 2^-9 max |v| = 9e-3 where few keys carry a row, may pass the
-    # bound (2.23e-3; 2.25e-3 seen in 2 million outputs)
+    # (the same in bf16: BF16_ROWS)
     (40, 24, 8, 64, 32, "f32", 544, 10),
     (40, 8, 8, 64, 5, "f32", 544, 11),
 ]
@@ -179,3 +179,103 @@ def test_softmax_prefix_time_per_request_is_constant():
         us[B] = best
     print(f"[time] {us}")
     assert us[8192] <= 2 * 16 * us[512]
+
+
+def _softmax64(q, k, v, kc, vc, pl):
+    """The attention in 64 bits (lengths pl of the cache, then the block), and the
+    spread sum(p |v - out|) / sum(p) of every output: what weights off by a
+    relative e each can move it by is e / (1 - e) of that."""
+    B, L, Hq, d = q.shape
+    Hkv = k.shape[2]
+    G = Hq // Hkv
+    out, spread = (torch.empty(q.shape, dtype=torch.float64, device="cuda") for _ in range(2))
+    for b, n in enumerate(pl):
+        kb, vb = (torch.cat([c[b, :n], x[b]]).double().transpose(0, 1) for c, x in ((kc, k), (vc, v)))
+        qb = q[b].double().transpose(0, 1).reshape(Hkv, G * L, d)
+        p = torch.softmax(torch.matmul(qb, kb.transpose(1, 2).contiguous()) / np.sqrt(d), -1)
+        o = torch.matmul(p, vb.contiguous())
+        # (over the value columns, in slices)
+        sp = torch.stack([(p * (vb[:, None, :, c] - o[:, :, None, c]).abs()).sum(-1) for c in range(d)], -1)
+        out[b], spread[b] = (x.reshape(Hq, L, d).transpose(0, 1) for x in (o, sp))
+    return out, spread
+
+
+def _check_rounded_weights(got, out, spread, dt, what):
+    """fp32: 1e-5.  bf16: the weights' rounding, at most 2^-8 each, and fp32
+    sums."""
+    err = (got.double() - out).abs()
+    tol = 2 ** -8 / (1 - 2 ** -8) * spread + 1e-5 if dt == "bf16" else torch.full_like(err, 1e-5)
+    print(f"[parity] {what}: max abs err {float(err.max()):.3e}, of the bound {float((err / tol).max()):.2f}; "
+          f"2e-2 rms is {2e-2 * float(out.square().mean().sqrt()):.2e}")
+    assert (err <= tol).all()
+
+
+BF16_ROWS = [(40, 24, 8, 64, 32, 544, 10), (40, 8, 8, 64, 5, 544, 11)]
+
+
+@pytest.mark.parametrize("case", BF16_ROWS, ids=lambda s: "x".join(map(str, s)))
+def test_softmax_prefix_few_keys_bf16(case):
+    """Rows that few keys carry, where the rounding of single weights shows."""
+    B, Hq, Hkv, d, L, Pmax, seed = case
+    announce(f"softmax_prefix few keys {case}")
+    pl = np.random.default_rng(seed).integers(0, Pmax + 1, B)
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rnd = lambda *n: torch.randn(n, generator=g, device="cuda").to(torch.bfloat16)
+    q, k, v = rnd(B, L, Hq, d), rnd(B, L, Hkv, d), rnd(B, L, Hkv, d)
+    kc, vc = rnd(B, Pmax, Hkv, d), rnd(B, Pmax, Hkv, d)
+    got = hb.softmax_prefix_step(q, k, v, kc, vc, i32(pl), out_f32=True)
+    _check_rounded_weights(got, *_softmax64(q, k, v, kc, vc, pl.tolist()), "bf16", f"few keys {case}")
+
+
+PLANNED = [
+    # (B, Hq, Hkv, d, L, dtype, Pmax, the longest request's ranges: at least)
+    # one request of Pmax keys among short ones: the plan alone cuts it
+    (24, 8, 8, 64, 4, "bf16", 4096, 5),       # one wave; 3 rounds < B * n_split
+    (24, 16, 8, 64, 9, "bf16", 4096, 5),
+    (24, 16, 4, 128, 32, "bf16", 4096, 5),
+    (24, 16, 2, 128, 32, "bf16", 4096, 5),    # 8 heads per KV head
+    (24, 12, 4, 64, 32, "bf16", 4096, 5),     # register-staged
+    (24, 8, 8, 64, 5, "f32", 4096, 5),
+    (24, 16, 4, 128, 5, "f32", 4096, 3),
+    (300, 6, 2, 64, 3, "bf16", 1184, 2),      # more requests than are staged in LDS
+    # more requests than three rounds: only the last candidate fits, whole requests
+    (50, 32, 32, 64, 3, "bf16", 800, 1),
+]
+
+
+@pytest.mark.parametrize("case", PLANNED, ids=lambda s: "x".join(map(str, s)))
+def test_softmax_prefix_planned_ranges(case):
+    """Calls that the device plans, contiguous and over permuted pages: the same
+    bits, within the bound, and the first request's number of ranges, read off
+    the partial results that they leave in the workspace (the second request, of
+    one range, leaves none)."""
+    B, Hq, Hkv, d, L, dt, Pmax, least = case
+    announce(f"softmax_prefix planned {case}")
+    act_t = torch.bfloat16 if dt == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(311)
+    rnd = lambda *n: torch.randn(n, generator=g, device="cuda").to(act_t)
+    pl = np.random.default_rng(312).integers(0, 64, B)
+    pl[0], pl[1] = Pmax, 3
+    if least > 1:
+        pl[B // 2], pl[-1] = Pmax // 2 + 7, Pmax - 31
+    q, k, v = rnd(B, L, Hq, d), rnd(B, L, Hkv, d), rnd(B, L, Hkv, d)
+    kc, vc = rnd(B, Pmax, Hkv, d), rnd(B, Pmax, Hkv, d)
+    dims = hb.make_dims(B, Hq, Hkv, d, L, 64, hb.HYB_BF16 if dt == "bf16" else hb.HYB_F32, 1)
+    ws = torch.full((hb.workspace_bytes(dims, hb.OP_SOFTMAX_PREFIX, Pmax) // 4,), float("nan"), device="cuda")
+    got = hb.softmax_prefix_step(q, k, v, kc, vc, i32(pl), out_f32=True, ws=ws)
+    torch.cuda.synchronize()
+    _check_rounded_weights(got, *_softmax64(q, k, v, kc, vc, pl.tolist()), dt, f"planned {case}")
+    per = ws.numel() // (B * Hq * L * (d + 2))      # ranges per request that fit
+    sums = ws[B * per * Hq * L * d:].view(B * per, -1)
+    written = ~torch.isnan(sums).all(1)
+    n = int((~written).nonzero()[0]) if not bool(written.all()) else B * per
+    print(f"[ranges] the first request: {n or 1}, written in all: {int(written.sum())} of {B * per}")
+    assert max(n, 1) >= least and (least > 1 or not written.any())
+    page = 32
+    order = torch.randperm(B * Pmax // page, generator=g, device="cuda")
+    pool = [torch.empty((order.numel(), page, Hkv, d), dtype=act_t, device="cuda") for _ in range(2)]
+    for dst, src in zip(pool, (kc, vc)):
+        dst[order] = src.view(dst.shape)
+    paged = hb.softmax_prefix_step_paged(q, k, v, *pool, order.to(torch.int32).view(B, -1), i32(pl), out_f32=True)
+    torch.cuda.synchronize()
+    assert torch.equal(got, paged)
