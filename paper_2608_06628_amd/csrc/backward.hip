@@ -32,10 +32,13 @@
 //   4. reverse walk with Gbar^T in the accumulators, the key part of dL/dW:
 //      hyb_bwd_rwalk_kernel on the bf16 path (pipelined, below),
 //      hyb_bwd_rev_kernel in walk mode on fp32;
-//   5. hyb_bwd_reduce_kernel: sums the per-(request, segment) partials in a
+//   5. with the input gradients, Gbar^T phi(K), the state part of dv: on the
+//      bf16 path hyb_bwd_dv_kernel (a second reverse walk, below), on fp32 by
+//      the walk of 4; then hyb_bwd_inputs_kernel: dq, dk and dv;
+//   6. hyb_bwd_reduce_kernel: sums the per-(request, segment) partials in a
 //      fixed order (bitwise reproducible, no atomics).
-// On the bf16 path phi(K), phi(Q) (as an update operand) and dL/du enter the
-// matrix products as bf16 pairs hi + lo; the state, Gbar and dL/dN as bf16.
+// On the bf16 path phi(K), phi(Q), dL/dN, dL/du, the state and Gbar enter the
+// matrix products as bf16 pairs hi + lo (three products where both operands are).
 #include <type_traits>
 
 #include "device.h"
@@ -2788,7 +2791,7 @@ __global__ __launch_bounds__(kWave*(D / kTile), sizeof(T) == 2 ? 2 : 1) void hyb
 }
 
 // ---------------------------------------------------------------------------
-// 5. Sum of the partials over requests and segments, in a fixed order.
+// Sum of the partials over requests and segments, in a fixed order.
 // ---------------------------------------------------------------------------
 __global__ void hyb_bwd_reduce_kernel(BwdKArgs ka) {
   const BackwardArgs& a = ka.a;

@@ -249,35 +249,10 @@ __device__ inline void store_out4(void* out, size_t idx, const float* v,
   }
 }
 
-// Eight consecutive outputs at element index idx (16-byte aligned), written
-// with non-temporal stores: fp32 as two 16-byte stores, bf16 as one.
-template <typename T>
-__device__ inline void store_out8_nt(void* out, size_t idx, const float* v,
-                                     bool f32) {
-  if (sizeof(T) == 4 || f32) {
-    f32x4* o = reinterpret_cast<f32x4*>((float*)out + idx);
-    __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, o);
-    __builtin_nontemporal_store(f32x4{v[4], v[5], v[6], v[7]}, o + 1);
-  } else {
-    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-    const bf16x8 x{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3],
-                   (bf16)v[4], (bf16)v[5], (bf16)v[6], (bf16)v[7]};
-    __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(&x),
-                                reinterpret_cast<u32x4*>((bf16*)out + idx));
-  }
-}
-
 // x as a bf16 pair in one dword: hi = bf16(x) in the low half, lo =
-// bf16(x - hi) in the high half (about 16 significant bits together).
-__device__ inline uint32_t pack_hi_lo(float x) {
-  const bf16 hi = (bf16)x;
-  const bf16 lo = (bf16)(x - (float)hi);
-  return (uint32_t)__builtin_bit_cast(uint16_t, hi) |
-         ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
-}
-// pack_hi_lo of two values at once: one paired rounding for the two hi parts
-// and one for the two lo parts, then one byte permute per result (the same
-// bits as two pack_hi_lo calls).
+// bf16(x - hi) in the high half (about 16 significant bits together).  Two
+// values at once: one paired rounding for the two hi parts and one for the two
+// lo parts, then one byte permute per result.
 __device__ inline void pack_hi_lo2(float x0, float x1, uint32_t& p0, uint32_t& p1) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   const uint32_t h = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)x0, (__bf16)x1});
@@ -291,34 +266,24 @@ __device__ inline float unpack_hi(uint32_t p) { return __builtin_bit_cast(float,
 __device__ inline float unpack_lo(uint32_t p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
 
 // The hi and lo operands of a row of packed pairs, elements in accumulator
-// order (as lds_op_perm): two runs of 4 consecutive entries.  Split into the
-// two reads and the unpacking, for callers that request many operands
-// before using them.
+// order (as lds_op_perm): two runs of 4 consecutive entries.
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-struct PairRaw {
-  u32x4 a, b;
-};
-__device__ inline PairRaw lds_pair_raw(const uint32_t* row, int ks, int hh) {
-  return PairRaw{*reinterpret_cast<const u32x4*>(row + 16 * ks + 4 * hh),
-                 *reinterpret_cast<const u32x4*>(row + 16 * ks + 8 + 4 * hh)};
-}
-__device__ inline void pair_split(const PairRaw& p, bf16x8& hi, bf16x8& lo) {
-  u32x4 h, l;
-  // low halves of consecutive dwords -> hi pieces, high halves -> lo pieces
-  h[0] = __builtin_amdgcn_perm(p.a[1], p.a[0], 0x05040100u);
-  h[1] = __builtin_amdgcn_perm(p.a[3], p.a[2], 0x05040100u);
-  h[2] = __builtin_amdgcn_perm(p.b[1], p.b[0], 0x05040100u);
-  h[3] = __builtin_amdgcn_perm(p.b[3], p.b[2], 0x05040100u);
-  l[0] = __builtin_amdgcn_perm(p.a[1], p.a[0], 0x07060302u);
-  l[1] = __builtin_amdgcn_perm(p.a[3], p.a[2], 0x07060302u);
-  l[2] = __builtin_amdgcn_perm(p.b[1], p.b[0], 0x07060302u);
-  l[3] = __builtin_amdgcn_perm(p.b[3], p.b[2], 0x07060302u);
-  hi = __builtin_bit_cast(bf16x8, h);
-  lo = __builtin_bit_cast(bf16x8, l);
-}
 __device__ inline void lds_pair_op(const uint32_t* row, int ks, int hh, bf16x8& hi,
                                    bf16x8& lo) {
-  pair_split(lds_pair_raw(row, ks, hh), hi, lo);
+  const u32x4 a = *reinterpret_cast<const u32x4*>(row + 16 * ks + 4 * hh);
+  const u32x4 b = *reinterpret_cast<const u32x4*>(row + 16 * ks + 8 + 4 * hh);
+  u32x4 h, l;
+  // low halves of consecutive dwords -> hi pieces, high halves -> lo pieces
+  h[0] = __builtin_amdgcn_perm(a[1], a[0], 0x05040100u);
+  h[1] = __builtin_amdgcn_perm(a[3], a[2], 0x05040100u);
+  h[2] = __builtin_amdgcn_perm(b[1], b[0], 0x05040100u);
+  h[3] = __builtin_amdgcn_perm(b[3], b[2], 0x05040100u);
+  l[0] = __builtin_amdgcn_perm(a[1], a[0], 0x07060302u);
+  l[1] = __builtin_amdgcn_perm(a[3], a[2], 0x07060302u);
+  l[2] = __builtin_amdgcn_perm(b[1], b[0], 0x07060302u);
+  l[3] = __builtin_amdgcn_perm(b[3], b[2], 0x07060302u);
+  hi = __builtin_bit_cast(bf16x8, h);
+  lo = __builtin_bit_cast(bf16x8, l);
 }
 
 // The same for 8 consecutive packed entries (natural order): row + 16*ks +
@@ -446,11 +411,6 @@ __device__ inline float log_sigmoid(float a) {
   return a >= 0.0f ? -log1pf(expf(-a)) : a - log1pf(expf(a));
 }
 
-// Workgroup barrier that orders LDS accesses only.  __syncthreads() carries a
-// workgroup fence over every address space, which makes each wave wait for
-// all of its outstanding global loads before the barrier; restricting the
-// fences to the local address space keeps loads issued before the barrier in
-// flight (LDS writes are still complete and visible after it).
 // Word 3 of a raw buffer resource on gfx9-family chips (32-bit data
 // format; the untyped loads and stores used here take no other field).
 constexpr int kBufferWord3 = 0x00020000;
@@ -467,6 +427,11 @@ __device__ inline void buf_to_lds16(__amdgpu_buffer_rsrc_t r, void* lds, int vof
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, soff, 0, 0);
 }
 
+// Workgroup barrier that orders LDS accesses only.  __syncthreads() carries a
+// workgroup fence over every address space, which makes each wave wait for
+// all of its outstanding global loads before the barrier; restricting the
+// fences to the local address space keeps loads issued before the barrier in
+// flight (LDS writes are still complete and visible after it).
 __device__ inline void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();

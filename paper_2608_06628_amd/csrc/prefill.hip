@@ -86,8 +86,8 @@ __device__ inline float* prefill_start_z(const PrefillArgs& a, const SegPlan& p,
 // segment walks; S, z + all pieces go back to S, z.  A unit whose slot is out
 // of range is skipped (its walk reads no starting state).
 // Bound by its bytes (64 KiB per unit, piece and segment at d = f = 128).  As
-// a pass of its own it costs 10 us at 8 x 8192 tokens (21 MB of increments),
-// where copying S and summing the pieces at each walk's start cost 12 us and
+// a pass of its own it costs 10 us at 8 x 8192 tokens (16.9 MB of increments,
+// 42 MB read and written), where copying S and summing the pieces at each walk's start cost 12 us and
 // a chain of loads per segment; that chain kept a prompt to 8 segments.
 template <bool FINAL>
 __global__ __launch_bounds__(256) void hyb_prefill_scan_kernel(PrefillArgs a, SegPlan p) {
@@ -447,7 +447,6 @@ struct PrefillPipeCfg {
   static constexpr int NT = F / kTile;
   static constexpr int NPAIR = 2 * NT;
   static constexpr int NRT = f / kTile;
-  static constexpr int ZPW = (NRT + NC - 1) / NC;  // z tiles per state wave
   static constexpr int KD = D / M::KW;
   static constexpr int KL = kTile / M::KW;
   static constexpr int KF = f / M::KW;
