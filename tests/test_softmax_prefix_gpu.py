@@ -279,3 +279,32 @@ def test_softmax_prefix_planned_ranges(case):
     paged = hb.softmax_prefix_step_paged(q, k, v, *pool, order.to(torch.int32).view(B, -1), i32(pl), out_f32=True)
     torch.cuda.synchronize()
     assert torch.equal(got, paged)
+
+
+def test_softmax_prefix_captured_plan():
+    """A captured call plans its ranges anew from the lengths of each replay.
+    The shape (6 heads per KV head) has no other test, so this is the first use
+    of its kernels: what they ask of the runtime is asked under capture."""
+    B, Hq, Hkv, d, L, Pmax = 24, 12, 2, 128, 7, 2048
+    announce("softmax_prefix captured plan")
+    g = torch.Generator(device="cuda").manual_seed(321)
+    rnd = lambda *n: torch.randn(n, generator=g, device="cuda").to(torch.bfloat16)
+    q, k, v = rnd(B, L, Hq, d), rnd(B, L, Hkv, d), rnd(B, L, Hkv, d)
+    kc, vc = rnd(B, Pmax, Hkv, d), rnd(B, Pmax, Hkv, d)
+    pl, out = i32(np.zeros(B)), torch.zeros_like(q)
+    dims = hb.make_dims(B, Hq, Hkv, d, L, 64, hb.HYB_BF16, 1)
+    ws = torch.empty(hb.workspace_bytes(dims, hb.OP_SOFTMAX_PREFIX, Pmax), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        hb.softmax_prefix_step(q, k, v, kc, vc, pl, out=out, ws=ws)
+    for i in range(4):
+        lens = np.random.default_rng(322 + i).integers(0, 64, B)
+        lens[i] = Pmax
+        pl.copy_(i32(lens))
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, hb.softmax_prefix_step(q, k, v, kc, vc, i32(lens)))
+        _check_rounded_weights(hb.softmax_prefix_step(q, k, v, kc, vc, i32(lens), out_f32=True),
+                               *_softmax64(q, k, v, kc, vc, lens.tolist()), "bf16", f"captured {i}")
